@@ -67,7 +67,10 @@ typedef struct spdp_matrix* spdp_handle_t;
  *                   (16 bytes, Sec. 4.2.3).
  *
  * Device memory for the four arrays plus a small split-K workspace is
- * allocated on the current device and owned by the handle. Returns
+ * allocated on the current device and owned by the handle; with tile_m = 256
+ * and tile_k >= 16 also 40 bytes per column of every stripe (columns rounded
+ * up to 64) for the kernels in which every column takes part (without them,
+ * where the memory cannot be had, such calls run the other kernels). Returns
  * SPDP_ERR_UNSUPPORTED if the padded values would take 4 GiB or more, or if
  * R * C * tile_k (GTile columns, plus one) reaches 2^26.
  */
@@ -92,7 +95,9 @@ int spdp_encode_host(const uint16_t* W, int64_t rows, int64_t cols,
  *              column k takes part for token b iff |X[b,k]| > threshold
  *              (strict). A negative threshold keeps every column; NaN is
  *              SPDP_ERR_INVALID_ARG. NaN activations are never active.
- *              Columns inactive for every token of the batch are not read.
+ *              Columns inactive for every token of the batch take no part
+ *              (with several tokens, where nearly every column is active for
+ *              some token, they may be read and multiplied by 0).
  *   Y          device, batch x rows fp16, row-major, fully overwritten with
  *              the fp32-accumulated result rounded once to nearest even.
  *              Must not overlap X.
@@ -112,7 +117,7 @@ int spdp_encode_host(const uint16_t* W, int64_t rows, int64_t cols,
  *
  * Deterministic: the fp32 summation order depends only on the matrix, the
  * batch and which columns are active (and on the tuning variables
- * SPDP_SPLITK, SPDP_PASSES, SPDP_MFMA and SPDP_EARLY_FIRST, when set), so
+ * SPDP_SPLITK, SPDP_PASSES, SPDP_MFMA, SPDP_WIDE and SPDP_EARLY_FIRST, when set), so
  * equal inputs give equal bits on every call, and a product gives the same
  * bits alone and inside spdp_spmspv_many.
  */
@@ -245,7 +250,9 @@ int spdp_reserve(spdp_handle_t h, int32_t max_batch);
  * s * passes * 4 * wave_cols on, so every column lies in exactly one range
  * (segments * passes * 4 * wave_cols >= cols). A property of the matrix and
  * the batch (and of the tuning variables SPDP_SPLITK and SPDP_PASSES), the
- * same on host-only handles. SPDP_ERR_INVALID_ARG for a NULL handle or
+ * same on host-only handles. Calls of several tokens in which every column
+ * takes part share the plan's workspace but may use fewer segments.
+ * SPDP_ERR_INVALID_ARG for a NULL handle or
  * output, or batch outside [1, 32]; the outputs are then unchanged.
  */
 int spdp_split_plan(spdp_handle_t h, int32_t batch, int32_t* segments,

@@ -45,6 +45,8 @@ def build(verbose: bool = False) -> str:
         # (the AGPR form would add registers and moves and cost occupancy)
         ([cc] + common + device + ["-mllvm", "-amdgpu-mfma-vgpr-form=true", "-c", os.path.join(CSRC, "spdp.hip"),
                                    "-o", os.path.join(objdir, "spdp.o")]),
+        ([cc] + common + device + ["-mllvm", "-amdgpu-mfma-vgpr-form=true", "-c", os.path.join(CSRC, "wide.hip"),
+                                   "-o", os.path.join(objdir, "wide.o")]),
         ([cc] + common + device + ["-c", os.path.join(CSRC, "spmm.hip"),
                                    "-o", os.path.join(objdir, "spmm.o")]),
     ]
@@ -67,8 +69,8 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError(failed)
     tmp = LIB + ".tmp"
     link = [cc, "-shared", f"--offload-arch={ARCH}", "-o", tmp,
-            os.path.join(objdir, "host.o"), os.path.join(objdir, "spdp.o"), os.path.join(objdir, "spmm.o"),
-            "-lpthread"]
+            os.path.join(objdir, "host.o"), os.path.join(objdir, "spdp.o"), os.path.join(objdir, "wide.o"),
+            os.path.join(objdir, "spmm.o"), "-lpthread"]
     res = subprocess.run(link, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(link)}\n{res.stdout}{res.stderr}")

@@ -31,6 +31,15 @@ struct spdp_matrix {
   void* d_values = nullptr;  // fp16 values or codes
   void* d_scales = nullptr;
 
+  // Word records of the kernels in which every column takes part (expand.h),
+  // [stripe][chunk], and the byte offset of each chunk's values; built for
+  // fp16 values with 256-row tiles and tile_k >= 16, else NULL.
+  void* d_rec = nullptr;
+  void* d_chunk_off = nullptr;
+  int chunks = 0;       // chunks (64 columns) of a stripe
+  int chunk_bytes = 0;  // LDS bytes that hold any chunk's values
+  bool finite = true;   // no infinity or NaN among the values (set with the records)
+
   // Split-K workspace: {fp32 partial sum, phase} pairs
   // [segments][batch][n_stripes*tile_m], and each row stripe's phase
   // (advanced on the device by every call).
@@ -58,5 +67,10 @@ int encode_host_arrays(const uint16_t* W, int64_t rows, int64_t cols,
 // (one fp32 scale per row) and stored one byte per code.
 int encode_host_arrays_rtn(const uint16_t* W, int64_t rows, int64_t cols,
                            int32_t tile_m, int32_t tile_k, int32_t bits, spdp_matrix* m);
+
+// Lays out the word records of a matrix whose arrays are on the device
+// (wide.hip); leaves d_rec NULL for tiles and value types they do not serve
+// and where their memory cannot be had.
+int build_records(spdp_matrix* m);
 
 }  // namespace spdp

@@ -56,6 +56,7 @@
 #include <string>
 
 #include "internal.h"
+#include "launch.h"
 
 namespace {
 
@@ -79,57 +80,6 @@ constexpr int kMaxBatch = 32;
 constexpr int kBmBytes = kBatch * kMaxWords * 8;          // bitmap words of one batch
 constexpr int kBatchBytes = kBatch * kSlotBytes + kBmBytes;  // one ring slot
 constexpr int kDmaPerBatch = kBatch / 2 + 1;  // 16-byte value loads (two columns each) + one bitmap load
-
-// One product of a launch: the matrix's device arrays, the call's input and
-// output, and the matrix's split.
-struct MatArgs {
-  const uint32_t* tile_offset;
-  const uint32_t* col_info;
-  const uint64_t* bitmap;
-  const uint16_t* values;  // fp16 values, or one-byte codes (the kernel's Q form)
-  const float* scales;     // Q form: one scale per row
-  const uint16_t* x;
-  uint16_t* y;
-  // [segments][batch][n_stripes * tile_m]: {fp32 bits, phase} pairs
-  unsigned long long* partials;
-  // the tag of this call's partials, never 0 (the workspace starts zeroed).
-  // A handle's own workspace has one phase per stripe (phase_step 1,
-  // epoch_done NULL): the tag is phase[r], and the stripe's first reducer
-  // advances it. The library's static workspace, shared by every handle, has
-  // one device-wide epoch (phase_step 0): the tag is *phase + 1 (0 skipped);
-  // each stripe's first reducer counts itself in *epoch_done, and the last
-  // stripe's stores the tag as the new epoch and clears the count.
-  uint32_t* phase;
-  uint32_t* epoch_done;
-  int phase_step;
-  int rows, cols;
-  int tile_m, tk_log2, n_colblocks, n_stripes;
-  int code;       // threshold code: active iff code < (x & 0x7fff) <= 0x7c00
-  int wave_cols;  // columns per wave (multiple of 16, <= kMaxWaveCols)
-  int segments;   // workgroups per row stripe
-  int n_wg;       // segments * n_stripes
-  uint32_t zero_col;  // column index whose bitmap lies in the zeroed tail padding
-  // nonzero: each wave requests its first batch before the workgroup list is
-  // built (a property of the product and the batch, never of the launch, so
-  // that grouping does not change the summation order)
-  int early_first;
-  // with the batch's shared column set (the kernel's BMASK form): a column
-  // is active iff the fp32 running sum of |x[b, k]| over the tokens exceeds
-  // batch_thr = fp32(batch * t), every token's activation kept there
-  float batch_thr;
-  // consecutive K ranges (of kWaves x wave_cols columns) per workgroup
-  int passes;
-};
-
-// A launch runs up to kMaxGroup independent products (same tile height and
-// batch): grid row y serves product y, its workgroup x being stripe
-// x / segments, segment x % segments (segments ascending within a stripe);
-// workgroups past the product's n_wg exit at once.
-constexpr int kMaxGroup = 8;
-struct LaunchArgs {
-  MatArgs m[kMaxGroup];
-  int batch;
-};
 
 // Per-wave ring of batch slots in LDS, filled by global->LDS DMA: deep enough
 // that at the Llama-7B shapes a wave's whole share is requested at once.
@@ -1220,7 +1170,7 @@ void release_device(spdp_matrix* m) {
   (void)hipSetDevice(m->device);
   (void)hipDeviceSynchronize();
   void* ptrs[] = {m->d_tile_offset, m->d_col_info, m->d_bitmap, m->d_values, m->d_scales, m->d_partials, m->d_phase,
-                  m->d_spmm_part};
+                  m->d_spmm_part, m->d_rec, m->d_chunk_off};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (void* p : m->retired) (void)hipFree(p);
@@ -1228,6 +1178,7 @@ void release_device(spdp_matrix* m) {
   m->d_tile_offset = m->d_col_info = m->d_bitmap = m->d_values = m->d_scales = nullptr;
   m->d_partials = nullptr;
   m->d_phase = nullptr;
+  m->d_rec = m->d_chunk_off = nullptr;
   m->partial_floats = 0;
   m->d_spmm_part = nullptr;
   m->spmm_part_bytes = 0;
@@ -1346,6 +1297,64 @@ int early_first(int batch, int64_t workgroups) {
   return workgroups <= kEarlyFirstMaxWorkgroups ? 1 : 0;
 }
 
+// The all-columns form (wide.hip) serves fp16 values in 256-row tiles
+// (records exist) where the columns that the batch leaves out cost less than
+// finding them. Measured at 0, 50 and 70 % activation sparsity, per-column ->
+// all-columns, us:
+//   per-token masks (at 70 % the union of 8 tokens has 94 % of the columns):
+//     8 tokens: 4096x4096 18.6 -> 12.4 (three grouped 37.0-38.2 -> 20.6),
+//     11008x4096 (two) 38.7-39.8 -> 35, 5120x13824 33.5-34.2 -> 25.7,
+//     28672x8192 69.0-73.8 -> 66.8; 16 and 32 tokens gain more (28672x8192 at
+//     32: 154 -> 85);
+//     5 tokens: 4096x4096 16.5-17.2 -> 11.9, 5120x13824 29.9-32.5 -> 25.4,
+//     11008x4096 (two) 32.8-36.5 -> 32.5, but 28672x8192 at 70 % 59.2 -> 65.6;
+//     4 tokens: 4096x4096 13.5-14.2 -> 11.8, 1024x8192 (three) 17.0-18.8 ->
+//     16.4, but 5120x13824 at 70 % 24.6 -> 25.5;
+//   one mask for the batch (25, 50 and 70 %): 8 and 16 tokens 4096x4096
+//     14.5-17.6 -> 13.6 and 17.0-19.7 -> 16.1, three grouped 28.8-35.2 -> 21.7
+//     and 36.2-45.5 -> 26.1; larger products lose (28672x8192 44.8 -> 71.7).
+// A matrix with infinities or NaNs stays with the per-column kernels, which
+// do not multiply a column that no token has active. A property of the
+// matrix, the batch and the mask, so a product gives the same bits alone and
+// grouped. SPDP_WIDE overrides the token count from which the form runs (0:
+// never; for tuning).
+constexpr int64_t kWideSmall = 20000000, kWideMedium = 100000000;  // weights, the zeros included
+bool use_wide(const spdp_matrix* h, int batch, bool bmask) {
+  if (!h->d_rec || !h->finite || batch < 2 || use_mfma(batch)) return false;
+  if (const char* env = std::getenv("SPDP_WIDE")) return std::atoi(env) > 0 && batch >= std::atoi(env);
+  const int64_t weights = h->rows * h->cols;
+  if (bmask) return batch >= 8 && weights <= kWideSmall;
+  return batch >= (weights <= kWideSmall ? 4 : weights <= kWideMedium ? 5 : 8);
+}
+
+// Chunks (64 columns) per segment of the all-columns form: at most `segments`
+// segments (the per-column plan's, so that the partials fit the same
+// workspace), the count that a model of the launch puts at the least time.
+// With m workgroups per CU (of 256), three of them resident, a chunk takes
+// 1.6, 1.75 or 2 us (one, two, three resident: from three on the vector ALUs
+// are the limit, 200 instructions per chunk and wave) and a workgroup 3 us
+// and 0.2 us per token (prologue; partials, 8 bytes per row and token).
+// Measured at 8 tokens, 70 % weight sparsity, us by segments: 28672x8192 4 /
+// 5 / 6 / 8: 69 / 75 / 66 / 66; 8192x28672 14 / 16 / 21: 68 / 62 / 66;
+// 13824x5120 (two grouped) 7 / 9 / 14: 46 / 43 / 46.
+int wide_seg_chunks(const spdp_matrix* h, int batch, int segments) {
+  const int64_t stripes = h->n_stripes;
+  int best = h->chunks;
+  float least = 0.0f;
+  for (int s = 1; s <= std::min(segments, h->chunks); ++s) {
+    const int per = (h->chunks + s - 1) / s;
+    if ((h->chunks + per - 1) / per != s) continue;
+    const int64_t m = (stripes * s + 255) / 256;
+    constexpr float kLast[3] = {0.0f, 1.6f, 1.75f};
+    const float us = (float)per * (2.0f * (float)(m / 3) + kLast[m % 3]) + (float)m * (3.0f + 0.2f * (float)batch);
+    if (s == 1 || us < least) {
+      least = us;
+      best = per;
+    }
+  }
+  return best;
+}
+
 // A split-K workspace that is not the handle's own: the library's static
 // one (partials and the device-wide epoch with its stripe count).
 struct SharedWorkspace {
@@ -1358,7 +1367,7 @@ struct SharedWorkspace {
 // Validates one product of a call and fills its kernel arguments: with the
 // handle's workspace (sized for the batch if needed), or with `shared`.
 int prepare(spdp_handle_t h, const uint16_t* X, int32_t batch, float threshold, int32_t mask, uint16_t* Y, int dev,
-            hipStream_t stream, const SharedWorkspace* shared, MatArgs* out, int64_t* n_wg) {
+            hipStream_t stream, const SharedWorkspace* shared, MatArgs* out, int64_t* n_wg, bool* wide) {
   if (!h) return fail(SPDP_ERR_INVALID_ARG, "handle is NULL");
   if (h->device < 0) return fail(SPDP_ERR_INVALID_ARG, "handle has no device copy");
   if (!X || !Y) return fail(SPDP_ERR_INVALID_ARG, "X or Y is NULL");
@@ -1415,6 +1424,16 @@ int prepare(spdp_handle_t h, const uint16_t* X, int32_t batch, float threshold, 
   *n_wg = (int64_t)segments * h->n_stripes;
   a.n_wg = (int)*n_wg;
   a.early_first = early_first(batch, *n_wg);
+  a.rec = static_cast<const unsigned char*>(h->d_rec);
+  a.chunk_off = static_cast<const uint32_t*>(h->d_chunk_off);
+  a.chunks = h->chunks;
+  *wide = use_wide(h, batch, mask == SPDP_MASK_BATCH && batch > 1);
+  if (*wide) {
+    a.seg_chunks = wide_seg_chunks(h, batch, segments);
+    a.segments = (h->chunks + a.seg_chunks - 1) / a.seg_chunks;
+    *n_wg = (int64_t)a.segments * h->n_stripes;
+    a.n_wg = (int)*n_wg;
+  }
   a.batch_thr = mask == SPDP_MASK_BATCH ? (float)((double)threshold * (double)batch) : 0.0f;
   return SPDP_OK;
 }
@@ -1452,6 +1471,7 @@ int finish_device(spdp_matrix* m, spdp_handle_t* out) {
   if (st == SPDP_OK) st = upload(m->bitmap, &m->d_bitmap);
   if (st == SPDP_OK) st = m->value_bits < 16 ? upload(m->codes, &m->d_values) : upload(m->values, &m->d_values);
   if (st == SPDP_OK && m->value_bits < 16) st = upload(m->scales, &m->d_scales);
+  if (st == SPDP_OK) st = spdp::build_records(m);
   if (st == SPDP_OK) {
     // every stripe starts in phase 1
     std::vector<uint32_t> ones((size_t)m->n_stripes, 1u);
@@ -1507,30 +1527,48 @@ int launch_products(const spdp_handle_t* handles, int32_t count, const uint16_t*
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  LaunchArgs la;
-  std::memset(&la, 0, sizeof(la));
-  la.batch = batch;
-  int64_t widest = 0;
+  // [0]: the per-column kernels' products, [1]: the all-columns form's
+  LaunchArgs args[2];
+  int counts[2] = {0, 0};
+  int64_t widest[2] = {0, 0};
+  std::memset(args, 0, sizeof(args));
+  args[0].batch = args[1].batch = batch;
   bool early = false, multi = false, wide = false;
   const bool bmask = mask == SPDP_MASK_BATCH && batch > 1;
   for (int i = 0; i < count; ++i) {
     int64_t n_wg = 0;
+    bool all_columns = false;
+    MatArgs m;
+    std::memset(&m, 0, sizeof(m));
     const int st = prepare(handles[i], X[i], batch, thresholds[i], mask, Y[i], dev, static_cast<hipStream_t>(stream),
-                           shared, &la.m[i], &n_wg);
+                           shared, &m, &n_wg, &all_columns);
     if (st != SPDP_OK) return st;
     if (handles[i]->tile_m != handles[0]->tile_m)
       return fail(SPDP_ERR_INVALID_ARG, "the matrices of one call must share tile_m");
     if ((handles[i]->value_bits < 16) != (handles[0]->value_bits < 16))
       return fail(SPDP_ERR_INVALID_ARG, "the matrices of one call must all hold fp16 values or all codes");
     if (n_wg >= (int64_t(1) << 31)) return fail(SPDP_ERR_UNSUPPORTED, "more than 2^31 - 1 workgroups");
-    widest = std::max(widest, n_wg);
-    early = early || la.m[i].early_first;
-    multi = multi || la.m[i].passes > 1;
-    wide = wide || la.m[i].wave_cols > kNarrowWaveCols;
+    const int k = all_columns ? 1 : 0;
+    args[k].m[counts[k]++] = m;
+    widest[k] = std::max(widest[k], n_wg);
+    if (all_columns) {
+      args[1].slot = std::max(args[1].slot, handles[i]->chunk_bytes);
+    } else {
+      early = early || m.early_first;
+      multi = multi || m.passes > 1;
+      wide = wide || m.wave_cols > kNarrowWaveCols;
+    }
   }
+  if (counts[1] > 0) {
+    e = launch_wide(args[1], counts[1], bmask, dim3((unsigned)widest[1], (unsigned)counts[1]),
+                    static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "kernel launch");
+    if (counts[0] == 0) return SPDP_OK;
+  }
+  const LaunchArgs& la = args[0];
 
   const int wpc = handles[0]->tile_m / 64;
-  const dim3 grid((unsigned)widest, (unsigned)count);
+  const dim3 grid((unsigned)widest[0], (unsigned)counts[0]);
   const bool q = handles[0]->value_bits < 16;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool mm = use_mfma(batch);
