@@ -207,9 +207,10 @@ int spdp_spmspv_many_mask(const spdp_handle_t* handles, int32_t count,
 /*
  * spdp_spmm -- the prefill product on the same encoded matrix (Sec. 4.3):
  * Y = X W_sp^T for n_tokens tokens, static pruning only (no activation
- * test: every column takes part), on the matrix cores: each 256 x 16 GTile
- * is expanded into a dense tile in LDS and multiplied with fp16 MFMA
- * instructions, fp32 accumulation, one rounding to fp16 (nearest even).
+ * test: every column takes part), on the matrix cores: the bitmap words
+ * are expanded into dense fp16 MFMA operands (few tokens: in registers;
+ * more: through a tile in LDS), fp32 accumulation, one rounding to fp16
+ * (nearest even).
  *
  *   h          handle from spdp_encode with tile_m = 256 and tile_k >= 16
  *              (a power of two); fp16 Values. Other handles:
@@ -222,11 +223,12 @@ int spdp_spmspv_many_mask(const spdp_handle_t* handles, int32_t count,
  *
  * Asynchronous. When the grid of (256-row stripe, token tile) pairs
  * leaves compute units idle (few tokens), or when a stripe has more than
- * 1799 GTiles, the columns are split into k <= 8 ranges (more for very wide
- * matrices; never more workgroups than the device has compute units): one kernel writes k fp32 partial products into a workspace of
- * the handle (k * n_tokens * rows * 4 bytes) and a second adds them in
- * range order and rounds once to fp16. That workspace grows on the first
- * call that needs more (hipMalloc; the old one is kept until spdp_free,
+ * 1799 GTiles, the columns are split into k <= 16 ranges (more for very wide
+ * matrices): one kernel writes k fp32 partial products into a workspace of
+ * the handle (k * n_tokens * rows * 4 bytes; a growth also covers what calls
+ * with fewer tokens take, at most 40 MB more than its own) and a second
+ * adds them in range order and rounds once to fp16. That workspace grows on
+ * the first call that needs more (hipMalloc; the old one is kept until spdp_free,
  * so graphs captured earlier stay valid); growing it while `stream` is
  * being captured is refused with SPDP_ERR_INVALID_ARG (make one call with
  * at least as many tokens before the capture). SPDP_ERR_OOM if it cannot

@@ -1312,7 +1312,10 @@ int early_first(int batch, int64_t workgroups) {
 //     16.4, but 5120x13824 at 70 % 24.6 -> 25.5;
 //   one mask for the batch (25, 50 and 70 %): 8 and 16 tokens 4096x4096
 //     14.5-17.6 -> 13.6 and 17.0-19.7 -> 16.1, three grouped 28.8-35.2 -> 21.7
-//     and 36.2-45.5 -> 26.1; larger products lose (28672x8192 44.8 -> 71.7).
+//     and 36.2-45.5 -> 26.1; larger products lose (28672x8192 44.8 -> 71.7),
+//     and so do three grouped above 16 tokens, where every workgroup sums
+//     all tokens' scores (1792x1600 at 25 % and 25 tokens 20.7 -> 22.9,
+//     4096x4096 at 70 % and 32 43.7 -> 46.5).
 // A matrix with infinities or NaNs stays with the per-column kernels, which
 // do not multiply a column that no token has active. A property of the
 // matrix, the batch and the mask, so a product gives the same bits alone and
@@ -1323,7 +1326,7 @@ bool use_wide(const spdp_matrix* h, int batch, bool bmask) {
   if (!h->d_rec || !h->finite || batch < 2 || use_mfma(batch)) return false;
   if (const char* env = std::getenv("SPDP_WIDE")) return std::atoi(env) > 0 && batch >= std::atoi(env);
   const int64_t weights = h->rows * h->cols;
-  if (bmask) return batch >= 8 && weights <= kWideSmall;
+  if (bmask) return batch >= 8 && batch <= 16 && weights <= kWideSmall;
   return batch >= (weights <= kWideSmall ? 4 : weights <= kWideMedium ? 5 : 8);
 }
 

@@ -5,21 +5,24 @@
 // (the paper's layout-alignment stage), then multiplied with
 // v_mfma_f32_32x32x16_f16 (fp16 operands, fp32 accumulation).
 //
-// A workgroup owns one 256-row stripe x 128 tokens and walks the stripe in
-// k-steps of 16 columns. Expansion of a k-step: lane i of bitmap word v of
-// a column takes row 64 v + i; its value sits at the word's masked popcount
-// below bit i plus the popcounts of the column's earlier words (HAD-SMBD,
-// Sec. 4.2.1), or is 0 where the bit is clear; the tile is row-major, 16
-// fp16 per row, rows padded to 40 bytes so that the MFMA operand reads of
-// 32 consecutive rows spread over the banks.
+// Expansion: lane i of bitmap word v of a column takes row 64 v + i; its
+// value sits at the word's masked popcount below bit i plus the popcounts of
+// the column's earlier words (HAD-SMBD, Sec. 4.2.1), or is 0 where the bit is
+// clear.
 //
-// Two forms:
-//   * spmm_kernel, any tile_k >= 16 and any width: four waves, each expands
-//     four columns and multiplies the stripe's eight 32-row blocks with its
-//     32 tokens; operands fetched one step ahead into registers;
-//   * spmm_ws_kernel, 256 x 16 GTiles and a width that is a multiple of 8:
-//     warp-specialized, DMA ring, split-K over the GTiles when the grid is
-//     small (described at the kernel).
+// The forms (choose_spmm picks one):
+//   * spmm_rows_kernel, for few tokens (tile_k >= 16, any width): every wave
+//     expands 64 rows straight into MFMA operands (expand.h), no tile in LDS;
+//   * spmm_ws_kernel and spmm_ws256_kernel, 256 x 16 GTiles and a width that
+//     is a multiple of 8: warp-specialized, the GTile expanded once into a
+//     dense tile in LDS (row-major, 16 fp16 per row, rows padded to 40 bytes
+//     so that the MFMA operand reads of 32 consecutive rows spread over the
+//     banks) for 128 or 256 tokens (described at the kernels);
+//   * spmm_kernel, the plain form: four waves, a 256-row stripe x 128 tokens,
+//     k-steps of 16 columns; each wave expands four columns of the tile and
+//     multiplies it with its 32 tokens, operands fetched one step ahead into
+//     registers. For handles without word records.
+// The first three split K when their grid is small.
 
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -29,6 +32,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "expand.h"
 #include "internal.h"
 
 namespace {
@@ -269,6 +273,35 @@ struct WsArgs {
   int sps;      // GTiles per split
 };
 
+// A wave's 64 rows x 32 NJ tokens from row m0 and token n0: the tokens are the
+// MFMA's rows, so register e of block (i, j) holds row 32 i + lane % 32 and
+// token 32 j + 8 (e / 4) + 4 (lane / 32) + e % 4, and a store writes 32
+// consecutive rows of two tokens (with the rows as the MFMA's rows a store
+// wrote four rows of 32 tokens each, elements one by one where the row count
+// is no multiple of 4: 5003x3080 at 333 / 1000 tokens
+// 69 / 101 -> 49 / 71 us; whole multiples of 4 within 2 %).
+template <int NJ>
+__device__ __forceinline__ void store_block(const WsArgs& wa, const float16v (&acc)[2][NJ], int m0, long long n0, int lane) {
+  const SpmmArgs& a = wa.s;
+  float* const part = wa.k_splits > 1 ? wa.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows : nullptr;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = m0 + 32 * i + (lane & 31);
+    if (m >= a.rows) continue;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const long long n = n0 + 32 * j + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        if (n >= a.n_tokens) continue;
+        if (part)
+          part[n * (long long)a.rows + m] = acc[i][j][e];
+        else
+          a.y[n * (long long)a.rows + m] = __half_as_ushort(__float2half_rn(acc[i][j][e]));
+      }
+  }
+}
+
 __global__ __launch_bounds__(kWsWaves * 64) void spmm_ws_kernel(WsArgs wa) {
   const SpmmArgs& a = wa.s;
   __shared__ __attribute__((aligned(1024))) unsigned char ring[kWsRing][kGBytes];
@@ -413,7 +446,7 @@ __global__ __launch_bounds__(kWsWaves * 64) void spmm_ws_kernel(WsArgs wa) {
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[i], b[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[j], av[i], acc[i][j], 0, 0, 0);
       if (kSteady || s + kWsRing - 1 < steps) issue(s + kWsRing - 1);
       if constexpr (kSteady)
         wait_vmcnt<kWsDma * (kWsRing - 3)>();
@@ -457,45 +490,7 @@ __global__ __launch_bounds__(kWsWaves * 64) void spmm_ws_kernel(WsArgs wa) {
   }
 
   if (!mma) return;
-  // accumulator register e of block (i, j) holds row 32 i + 8 (e / 4) +
-  // 4 (lane / 32) + e % 4 of the wave's 64 rows and token 32 j + lane % 32
-  float* const part = wa.k_splits > 1 ? wa.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows : nullptr;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const long long n = nb0 + 64 * th + 32 * j + (lane & 31);
-    if (n >= a.n_tokens) continue;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        const int m = r * kTM + 64 * rq + 32 * i + 8 * grp + 4 * (lane >> 5);
-        if (part) {
-          float* const prow = part + n * (long long)a.rows;
-          if (a.y_vec && m + 3 < a.rows) {
-            *reinterpret_cast<float4*>(prow + m) = make_float4(acc[i][j][4 * grp], acc[i][j][4 * grp + 1],
-                                                               acc[i][j][4 * grp + 2], acc[i][j][4 * grp + 3]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (m + e < a.rows) prow[m + e] = acc[i][j][4 * grp + e];
-          }
-          continue;
-        }
-        uint16_t* const yrow = a.y + n * (long long)a.rows;
-        uint16_t hh[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hh[e] = __half_as_ushort(__float2half_rn(acc[i][j][4 * grp + e]));
-        if (a.y_vec && m + 3 < a.rows) {
-          *reinterpret_cast<uint2*>(yrow + m) =
-              make_uint2(hh[0] | ((uint32_t)hh[1] << 16), hh[2] | ((uint32_t)hh[3] << 16));
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (m + e < a.rows) yrow[m + e] = hh[e];
-        }
-      }
-    }
-  }
+  store_block<2>(wa, acc, r * kTM + 64 * rq, nb0 + 64 * th, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -585,7 +580,7 @@ __global__ __launch_bounds__(kW256Waves * 64) void spmm_ws256_kernel(WsArgs wa) 
         half8 b = *reinterpret_cast<const half8*>(slot + kValBytes + (128 * th + 32 * j + (lane & 31)) * 32 + 2 * khalf);
         if (zero_b) b = none;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[i], b, acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, av[i], acc[i][j], 0, 0, 0);
       }
       if (kSteady || s + R - 1 < steps) issue(s + R - 1);
       if constexpr (kSteady)
@@ -603,43 +598,7 @@ __global__ __launch_bounds__(kW256Waves * 64) void spmm_ws256_kernel(WsArgs wa) 
     for (; s < steady_end; ++s) step(s, std::integral_constant<bool, true>{});
     for (; s < steps; ++s) step(s, std::integral_constant<bool, false>{});
 
-    float* const part = wa.k_splits > 1 ? wa.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows : nullptr;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const long long n = nb0 + 128 * th + 32 * j + (lane & 31);
-      if (n >= a.n_tokens) continue;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-          const int m = r * kTM + 64 * rq + 32 * i + 8 * grp + 4 * (lane >> 5);
-          if (part) {
-            float* const prow = part + n * (long long)a.rows;
-            if (a.y_vec && m + 3 < a.rows) {
-              *reinterpret_cast<float4*>(prow + m) = make_float4(acc[i][j][4 * grp], acc[i][j][4 * grp + 1],
-                                                                 acc[i][j][4 * grp + 2], acc[i][j][4 * grp + 3]);
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (m + e < a.rows) prow[m + e] = acc[i][j][4 * grp + e];
-            }
-            continue;
-          }
-          uint16_t* const yrow = a.y + n * (long long)a.rows;
-          uint16_t hh[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) hh[e] = __half_as_ushort(__float2half_rn(acc[i][j][4 * grp + e]));
-          if (a.y_vec && m + 3 < a.rows) {
-            *reinterpret_cast<uint2*>(yrow + m) =
-                make_uint2(hh[0] | ((uint32_t)hh[1] << 16), hh[2] | ((uint32_t)hh[3] << 16));
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (m + e < a.rows) yrow[m + e] = hh[e];
-          }
-        }
-      }
-    }
+    store_block<4>(wa, acc, r * kTM + 64 * rq, nb0 + 128 * th, lane);
   } else {
     // ---- expanding waves
     const int d = wave - 8;
@@ -714,6 +673,180 @@ __global__ __launch_bounds__(kW256Waves * 64) void spmm_ws256_kernel(WsArgs wa) 
   }
 }
 
+// ---------------------------------------------------------------------------
+// Row form, for few tokens: nothing is expanded into LDS. A workgroup of
+// eight waves owns a stripe and 32 TB tokens; wave w expands bitmap word
+// w mod 4 (64 rows) of the groups 2 (w / 4), 2 (w / 4) + 1 of every chunk (64
+// columns) straight into MFMA operands (expand.h) and multiplies them with
+// all the tokens; the chunk's two halves are added once, at the end. One
+// barrier per chunk; values and X arrive by DMA one chunk ahead.
+
+template <int TB>
+struct RowCfg {
+  static constexpr int kTokens = 32 * TB;
+  static constexpr int kXBytes = kTokens * spdp_dev::kChunkCols * 2;
+  static constexpr int kRedBytes = 8 * TB * 16 * 64 * 4;  // half of every wave's accumulators
+  static int lds(int slot) { return std::max(2 * (slot + kXBytes) + 1024, kRedBytes); }
+};
+
+struct RowArgs {
+  const unsigned char* rec;   // word records, [stripe][chunk][group][word]
+  const uint32_t* chunk_off;  // byte offset of each chunk's values, [stripe][chunk], one more at the end
+  const uint16_t* values;
+  const uint16_t* x;  // [n_tokens][cols]
+  uint16_t* y;        // [n_tokens][rows]
+  float* part;        // [splits][n_tokens][rows] fp32 with more than one split
+  long long n_tokens;
+  int rows, cols;
+  int chunks;         // chunks of a stripe
+  int cps;            // chunks per split
+  int slot;           // LDS bytes of a chunk's values (a multiple of 1024)
+};
+
+// XV: X rows are 16-byte aligned (else they are read by elements).
+template <int TB, bool XV>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TB == 1 ? 6 : 4))) void spmm_rows_kernel(RowArgs a) {
+  using namespace spdp_dev;
+  using C = RowCfg<TB>;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int word = wave & 3, half = wave >> 2;
+  const int r = blockIdx.x;
+  const long long nb0 = (long long)blockIdx.y * C::kTokens;
+  const int last_tok = (int)min(a.n_tokens - nb0, (long long)C::kTokens) - 1;
+  const int c0 = (int)blockIdx.z * a.cps;
+  const int n = min(a.cps, a.chunks - c0);  // >= 1
+  const uint32_t chunk0 = (uint32_t)r * (uint32_t)a.chunks + (uint32_t)c0;
+  const uint32_t l0 = lds_addr(lds);
+  const uint32_t slot = (uint32_t)a.slot;
+  const uint32_t x0 = l0 + 2 * slot;
+  const const_ptr<uint32_t> co = (const_ptr<uint32_t>)a.chunk_off + chunk0;
+  const unsigned char* const rec0 = a.rec + (size_t)chunk0 * kChunkRecBytes;
+  const uint16_t* const xb = a.x + nb0 * (long long)a.cols;
+
+  // requests the values [t0, t1) and the X block of chunk s, and the records
+  // of chunk s + 1 into L2 (landing where nobody reads). X: 128 bytes per
+  // token, its 16-byte piece p at position p ^ (token mod 8); wave w brings
+  // the tokens 8 w .. 8 w + 7 (TB = 1: the first four waves)
+  const int piece = (lane & 7) ^ (lane >> 3);
+  auto issue = [&](int s, uint32_t t0, uint32_t t1) __attribute__((always_inline)) {
+    const uint32_t last = t1 > t0 ? t1 - t0 - 16u : 0u;
+    const uint32_t vl = l0 + (uint32_t)(s & 1) * slot;
+    for (uint32_t q0 = 1024u * (uint32_t)wave; q0 <= last; q0 += 8192u)
+      dma16(a.values, t0 + min(q0 + 16u * (uint32_t)lane, last),
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)(vl + q0)));
+    if (TB == 2 || wave < 4) {
+      const uint32_t to = x0 + (uint32_t)((s & 1) * C::kXBytes + 1024 * wave);
+      const uint32_t t = (uint32_t)min(8 * wave + (lane >> 3), last_tok);
+      const int k = (c0 + s) * kChunkCols + 8 * piece;
+      if constexpr (XV) {
+        // pieces past the width are cleared (0 x a neighbour's infinity must
+        // not reach the sums)
+        if (k < a.cols)
+          dma16(xb, (t * (uint32_t)a.cols + (uint32_t)k) * 2u, (uint32_t)__builtin_amdgcn_readfirstlane((int)to));
+        else
+          *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(to + 16u * (uint32_t)lane) = u32x4{0, 0, 0, 0};
+      } else {
+        uint32_t h[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) h[e] = k + e < a.cols ? xb[(size_t)t * a.cols + k + e] : 0u;
+        *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(to + 16u * (uint32_t)lane) =
+            u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+      }
+    }
+    const int wr = wave - 5;
+    if (wr >= 0)
+      dma16(rec0, (uint32_t)(s + 1) * kChunkRecBytes + min(1024u * (uint32_t)wr + 16u * (uint32_t)lane, (uint32_t)kChunkRecBytes - 16u),
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)(x0 + 2 * C::kXBytes)));
+  };
+
+  float16v acc[2][TB];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TB; ++j) acc[i][j] = float16v{};
+  const_ptr<unsigned char> prec = (const_ptr<unsigned char>)rec0 + (size_t)((8 * half + word) * kRecBytes);
+  WordRec m;
+  auto fetch = [&](uint32_t step) __attribute__((always_inline)) {
+    asm volatile("" : "+s"(prec));
+    load_rec(prec, m);
+    prec += step;
+  };
+  const uint32_t xlane = x0 + 128u * (uint32_t)(lane & 31);
+  const uint32_t xpos = 16u * (uint32_t)(((lane >> 5) | (4 * half)) ^ (lane & 7));
+
+  uint32_t t0 = co[0], t1 = co[1];
+  issue(0, t0, t1);
+  fetch(4 * kRecBytes);
+  t0 = t1;
+  t1 = co[min(2, n)];
+  for (int s = 0; s < n; ++s) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (s + 1 < n) issue(s + 1, t0, t1);
+    uint32_t base2 = (l0 + (uint32_t)(s & 1) * slot) >> 1;
+    asm volatile("" : "+v"(base2));
+    const uint32_t xm = xlane + (uint32_t)((s & 1) * C::kXBytes);
+    uint32_t t_next = 0;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      uint32_t v[kGroupCols];
+      half8 x[TB];
+#pragma unroll
+      for (int c = 0; c < kGroupCols; ++c) v[c] = gather_column(m, c, base2);
+#pragma unroll
+      for (int j = 0; j < TB; ++j)
+        x[j] = *(const __attribute__((address_space(3))) half8*)(uintptr_t)(xm + (xpos ^ (32u * g)) + 4096u * (uint32_t)j);
+      __builtin_amdgcn_sched_barrier(0);
+      Operands o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) select_pairs(m, v, j, o);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(g == 0 ? 12 * kRecBytes : 4 * kRecBytes);
+      if (g == 1) t_next = co[min(s + 3, n)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[j], o.rows(i), acc[i][j], 0, 0, 0);
+    }
+    t0 = t1;
+    t1 = t_next;
+  }
+
+  // the two halves' sums: wave (word, 0) takes rows 0-31 of the word, wave
+  // (word, 1) rows 32-63, each the sum half 0 + half 1. Register e holds row
+  // lane mod 32 and token 32 j + 8 (e / 4) + 4 (lane / 32) + e mod 4: a store
+  // writes 32 consecutive rows of two tokens.
+  __syncthreads();
+  float* const red = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int j = 0; j < TB; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      red[((wave * TB + j) * 16 + e) * 64 + lane] = half == 0 ? acc[1][j][e] : acc[0][j][e];
+  __syncthreads();
+  const int row = r * kTM + 64 * word + 32 * half + (lane & 31);
+  if (row >= a.rows) return;
+  const bool split = gridDim.z > 1;
+  float* const part = a.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows;
+#pragma unroll
+  for (int j = 0; j < TB; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float other = red[(((wave ^ 4) * TB + j) * 16 + e) * 64 + lane];
+      const float sum = half == 0 ? acc[0][j][e] + other : other + acc[1][j][e];
+      const int t = 32 * j + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      if (t > last_tok) continue;
+      const size_t at = (size_t)(nb0 + t) * (size_t)a.rows + (size_t)row;
+      if (split)
+        part[at] = sum;
+      else
+        a.y[at] = __half_as_ushort(__float2half_rn(sum));
+    }
+}
+
 // Y = fp16(sum over the splits of part[z]), the splits added in order
 // (z = 0, 1, ...), so the result does not depend on timing. Four outputs
 // per lane when the element count is a multiple of 4.
@@ -748,11 +881,153 @@ int hip_fail(hipError_t e, const char* what) {
   return spdp::fail(SPDP_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// How a prefill product is run: the kernel, its token tiles, and the splits
+// of `per` GTiles (the row form: chunks) each.
+enum { kFormPlain = 1, kFormWs128, kFormWs256, kFormRows32, kFormRows64 };
+struct SpmmPlan {
+  int form;
+  long long tiles;
+  int splits, per;
+  int keep;  // the splits that the warp-specialized rule would take
+};
+
+// us to write and add `splits` partial products (a second launch, 4 bytes
+// written and read per value at the rate of a large copy)
+float split_us(int splits, long long n_tokens, long long rows) {
+  return splits > 1 ? 3.0f + (float)splits * (float)n_tokens * (float)rows * 8.0f / 4.0e6f : 0.0f;
+}
+
+// The splits of the row form are bounded by the grid, and so that its
+// partials stay within those of 128 tokens at that many splits and within
+// 40 MB (a larger bound gave no shape less time, and the first call
+// allocates it: 11008x4096 at 512 tokens 62 MB -> 45 MB, the
+// warp-specialized form's own).
+int row_max_splits(const spdp_matrix* h) { return (int)std::min<long long>(16, std::max<long long>(1, 512 / h->n_stripes)); }
+long long row_part_tokens(const spdp_matrix* h) {
+  return std::min<long long>(128ll * row_max_splits(h), 10000000ll / h->rows);
+}
+
+// The row form's least time over its splits (us; fills the plan): with m
+// workgroups per CU a chunk takes 1.2 / 1.6 / 1.9 us at 32 tokens (one, two,
+// three resident), 1.33 / 1.75 at 64 (one, two); 2 and 3 us per workgroup.
+float row_us(const spdp_matrix* h, long long n_tokens, int cus, int tb, int forced, SpmmPlan* plan) {
+  const long long tiles = (n_tokens + 32 * tb - 1) / (32 * tb);
+  const int most = forced > 0 ? std::min(forced, h->chunks)
+                              : std::max(1, (int)std::min<long long>(row_max_splits(h), row_part_tokens(h) / n_tokens));
+  float least = -1.0f;
+  for (int k = forced > 0 ? most : 1; k <= std::min(most, h->chunks); ++k) {
+    const int per = (h->chunks + k - 1) / k;
+    const int splits = (h->chunks + per - 1) / per;
+    const long long m = (h->n_stripes * tiles * splits + cus - 1) / cus;
+    constexpr float kLast32[3] = {0.0f, 1.2f, 1.6f};
+    const float chunk = tb == 1 ? 1.9f * (float)(m / 3) + kLast32[m % 3] : 1.75f * (float)(m / 2) + (m % 2 ? 1.33f : 0.0f);
+    const float us = (float)per * chunk + (tb == 1 ? 2.0f : 3.0f) * (float)m + split_us(splits, n_tokens, h->rows);
+    if (least < 0.0f || us < least) {
+      least = us;
+      plan->form = tb == 1 ? kFormRows32 : kFormRows64;
+      plan->tiles = tiles;
+      plan->splits = splits;
+      plan->per = per;
+    }
+  }
+  return least;
+}
+
+// The warp-specialized forms: 256-token workgroups above 128 tokens when
+// their grid, split, covers at least half the CUs (the expansion of a GTile
+// is paid once per workgroup; below that the 128-token form's larger grid
+// wins); split K when the (stripe, token tile) grid leaves CUs idle, so that
+// a split's TileOffsets fit the LDS table, and with at least 8 GTiles per
+// split (40 for the 256-token form). A workgroup of either form holds its
+// CU, so the split never asks for more workgroups than there are CUs: a
+// second round for a few of them doubles the time. Measured (us; 256-token
+// workgroups only when two of them per CU were left unsplit and the split
+// rounded up -> this rule): 11008x4096 at 256 / 512 tokens 108 / 148 -> 57 /
+// 95, 8192x8192 at 512 149 -> 105, 28672x8192 at 512 334 -> 294, 4096x4096
+// at 1024 90 -> 77. Returns the time of the model: 0.5 us per GTile at 128
+// tokens, 0.55 at 256, and 2 us (4 at 128 tokens) per round.
+float ws_us(const spdp_matrix* h, long long n_tokens, int cus, int form, int forced, SpmmPlan* plan) {
+  const int ncb = (int)h->n_colblocks;
+  const long long tiles256 = (n_tokens + kBN256 - 1) / kBN256, tiles128 = (n_tokens + kBN - 1) / kBN;
+  const long long wgs256 = h->n_stripes * tiles256;
+  long long k256 = wgs256 < cus ? std::max<long long>(1, std::min<long long>(8, cus / wgs256)) : 1;
+  k256 = std::min<long long>(k256, std::max(1, ncb / 40));
+  const bool wide = form == kFormWs256 || (form != kFormWs128 && n_tokens > kBN && 2 * wgs256 * k256 >= cus);
+  const long long tiles = wide ? tiles256 : tiles128;
+  const long long wgs = h->n_stripes * tiles;
+  long long k = wide ? k256 : wgs < cus ? std::max<long long>(1, std::min<long long>(8, cus / wgs)) : 1;
+  if (!wide) k = std::min<long long>(k, std::max(1, ncb / 8));
+  if (forced > 0) k = forced;
+  k = std::max<long long>(k, (ncb + kToCap - 2) / (kToCap - 1));
+  k = std::min<long long>(k, ncb);
+  const int per = (int)((ncb + k - 1) / k);
+  plan->form = wide ? kFormWs256 : kFormWs128;
+  plan->tiles = tiles;
+  plan->per = per;
+  plan->splits = (ncb + per - 1) / per;  // every split non-empty
+  const float rounds = (float)((wgs * plan->splits + cus - 1) / cus);
+  return rounds * ((float)per * (wide ? 0.55f : 0.5f) + (wide ? 2.0f : 4.0f)) + split_us(plan->splits, n_tokens, h->rows);
+}
+
+// The form with the least modelled time. The row form needs the word
+// records, the warp-specialized ones 256 x 16 GTiles and a width that is a
+// multiple of 8; the plain one takes what is left. Measured, the
+// warp-specialized forms -> the row form, us: 4096x4096 at 16 / 64 / 128
+// tokens 25.1 / 25.8 / 29.4 -> 14.7 / 19.4 / 23.8 (at 333 44.7 -> 43.6, at 512
+// they tie), 4096x11008 at 64 / 256 53 / 66 -> 29 / 57, 11008x4096 at 32 / 64
+// 36.8 / 36.9 -> 25.6 / 31.1 (at 128 41.7 -> 44.5), 28672x8192 at 32 / 64 / 128
+// 138 / 134 / 139 -> 67 / 77 / 134 (at 256 173 -> 244). SPDP_SPMM_FORM (a
+// testing aid) forces a form: 1 plain, 2 and 3 the warp-specialized ones of
+// 128 and 256 tokens, 4 and 5 the row form of 32 and 64; SPDP_SPMM_SPLITS the
+// splits. False: more splits than a grid holds.
+bool choose_spmm(const spdp_matrix* h, long long n_tokens, int cus, bool x_vec, SpmmPlan* plan) {
+  int form = 0, forced = 0;
+  if (const char* env = std::getenv("SPDP_SPMM_FORM")) form = std::atoi(env);
+  if (const char* env = std::getenv("SPDP_SPMM_SPLITS")) forced = std::max(1, std::atoi(env));
+  const bool ws = h->tile_k == kKStep && x_vec && form != kFormPlain;
+  const bool rows = h->d_rec != nullptr && form != kFormPlain && (n_tokens + 31) / 32 <= 65535;
+  plan->form = kFormPlain;
+  plan->tiles = (n_tokens + kBN - 1) / kBN;
+  plan->splits = 1;
+  plan->per = 0;
+  plan->keep = 1;
+  float least = -1.0f;
+  if (ws) {
+    SpmmPlan p = *plan;
+    const float us = ws_us(h, n_tokens, cus, form, forced, &p);
+    p.keep = p.splits;
+    if (form != kFormRows32 && form != kFormRows64) {
+      least = us;
+      *plan = p;
+    } else {
+      plan->keep = p.splits;
+    }
+  }
+  if (rows && !(ws && (form == kFormWs128 || form == kFormWs256)))
+    for (int tb = 1; tb <= 2; ++tb) {
+      if ((form == kFormRows32 && tb != 1) || (form == kFormRows64 && tb != 2)) continue;
+      SpmmPlan p = *plan;
+      const float us = row_us(h, n_tokens, cus, tb, forced, &p);
+      if (least < 0.0f || us < least) {
+        least = us;
+        *plan = p;
+      }
+    }
+  return plan->splits <= 65535;
+}
+
 // The split-K partial sums of the prefill product: grown on demand, the
 // old buffer kept until the handle is freed (a captured graph may still
-// name it); no allocation while the stream is being captured.
-int ensure_spmm_part(spdp_matrix* h, size_t bytes, hipStream_t stream) {
-  if (bytes <= h->spmm_part_bytes) return SPDP_OK;
+// name it); no allocation while the stream is being captured. A growth also
+// covers what fewer tokens would take: the row form's
+// splits, and the warp-specialized rule's.
+int ensure_spmm_part(spdp_matrix* h, int splits, int keep, long long n_tokens, hipStream_t stream) {
+  const size_t row_bytes = (size_t)h->rows * sizeof(float);
+  if ((size_t)splits * (size_t)n_tokens * row_bytes <= h->spmm_part_bytes) return SPDP_OK;
+  size_t vectors = (size_t)std::max(splits, keep) * (size_t)n_tokens;
+  if (h->d_rec)
+    vectors = std::max(vectors, (size_t)std::min<long long>(row_max_splits(h) * n_tokens, row_part_tokens(h)));
+  const size_t bytes = vectors * row_bytes;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(stream, &cs);
   if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
@@ -769,6 +1044,23 @@ int ensure_spmm_part(spdp_matrix* h, size_t bytes, hipStream_t stream) {
   h->d_spmm_part = p;
   h->spmm_part_bytes = bytes;
   return SPDP_OK;
+}
+
+template <int TB, bool XV>
+hipError_t launch_rows_form(const RowArgs& a, dim3 grid, hipStream_t st) {
+  const int lds = RowCfg<TB>::lds(a.slot);
+  const auto kernel = spmm_rows_kernel<TB, XV>;
+  if (lds > 64 * 1024) {
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, grid, dim3(512), lds, st, a);
+  return hipGetLastError();
+}
+hipError_t launch_rows(const RowArgs& a, int tb, bool xv, dim3 grid, hipStream_t st) {
+  if (tb == 1) return xv ? launch_rows_form<1, true>(a, grid, st) : launch_rows_form<1, false>(a, grid, st);
+  return xv ? launch_rows_form<2, true>(a, grid, st) : launch_rows_form<2, false>(a, grid, st);
 }
 
 }  // namespace
@@ -812,71 +1104,57 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
   a.steps = (int)(h->n_colblocks * h->tile_k / kKStep);
   a.x_vec = h->cols % 8 == 0;
   a.y_vec = h->rows % 4 == 0;
-  const long long tok_tiles = (n_tokens + kBN - 1) / kBN;
   auto st = static_cast<hipStream_t>(stream);
-  // SPDP_SPMM_FORM (a testing aid): 1 the plain form, 2 the 128-token
-  // warp-specialized form, 3 the 256-token one
-  int form = 0;
-  if (const char* env = std::getenv("SPDP_SPMM_FORM")) form = std::atoi(env);
-  if (h->tile_k == kKStep && a.x_vec && form != 1) {
-    // 256-token workgroups above 128 tokens when their grid, split, covers
-    // at least half the CUs (the expansion of a GTile is paid once per
-    // workgroup; below that the 128-token form's larger grid wins); split K
-    // when the (stripe, token tile) grid leaves CUs idle, so that a split's
-    // TileOffsets fit the LDS table, and with at least 8 GTiles per split
-    // (40 for the 256-token form). A workgroup of either form holds its CU,
-    // so the split never asks for more workgroups than there are CUs: a
-    // second round for a few of them doubles the time. Measured (us; the
-    // previous rule, 256-token workgroups only when two of them per CU were
-    // left unsplit and the split rounded up -> this one): 11008x4096 at 128
-    // / 256 / 512 tokens 66 / 108 / 148 -> 42 / 57 / 95, 8192x8192 at 512
-    // 149 -> 105, 28672x8192 at 128 / 512 199 / 334 -> 145 / 294, 4096x4096
-    // at 1024 90 -> 77.
-    const int ncb = (int)h->n_colblocks;
-    int cus = 0;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
-    const long long tiles256 = (n_tokens + kBN256 - 1) / kBN256;
-    const long long wgs256 = h->n_stripes * tiles256;
-    long long k256 = wgs256 < cus ? std::max<long long>(1, std::min<long long>(8, cus / wgs256)) : 1;
-    k256 = std::min<long long>(k256, std::max(1, ncb / 40));
-    const bool wide = form == 3 || (form != 2 && n_tokens > kBN && 2 * wgs256 * k256 >= cus);
-    const long long tiles = wide ? tiles256 : tok_tiles;
-    const long long wgs = h->n_stripes * tiles;
-    long long k = wide ? k256 : wgs < cus ? std::max<long long>(1, std::min<long long>(8, cus / wgs)) : 1;
-    if (!wide) k = std::min<long long>(k, std::max(1, ncb / 8));
-    if (const char* env = std::getenv("SPDP_SPMM_SPLITS")) k = std::max(1, std::atoi(env));
-    k = std::max<long long>(k, (ncb + kToCap - 2) / (kToCap - 1));
-    k = std::min<long long>(k, ncb);
-    const int sps = (int)((ncb + k - 1) / k);
-    k = (ncb + sps - 1) / sps;  // every split non-empty
-    if (k > 65535) return fail(SPDP_ERR_UNSUPPORTED, "the width needs more than 65535 splits");
+  int cus = 0;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+  SpmmPlan plan;
+  if (!choose_spmm(h, n_tokens, cus, a.x_vec != 0, &plan))
+    return fail(SPDP_ERR_UNSUPPORTED, "the width needs more than 65535 splits");
+  float* part = nullptr;
+  if (plan.splits > 1) {
+    const int st_ok = ensure_spmm_part(h, plan.splits, plan.keep, n_tokens, st);
+    if (st_ok != SPDP_OK) return st_ok;
+    part = static_cast<float*>(h->d_spmm_part);
+  }
+  const dim3 grid((unsigned)h->n_stripes, (unsigned)plan.tiles, (unsigned)plan.splits);
+  if (plan.form == kFormRows32 || plan.form == kFormRows64) {
+    RowArgs ra;
+    std::memset(&ra, 0, sizeof(ra));
+    ra.rec = static_cast<const unsigned char*>(h->d_rec);
+    ra.chunk_off = static_cast<const uint32_t*>(h->d_chunk_off);
+    ra.values = a.values;
+    ra.x = X;
+    ra.y = Y;
+    ra.part = part;
+    ra.n_tokens = n_tokens;
+    ra.rows = a.rows;
+    ra.cols = a.cols;
+    ra.chunks = h->chunks;
+    ra.cps = plan.per;
+    ra.slot = h->chunk_bytes;
+    e = launch_rows(ra, plan.form == kFormRows32 ? 1 : 2, a.x_vec != 0, grid, st);
+  } else if (plan.form == kFormPlain) {
+    hipLaunchKernelGGL(spmm_kernel, grid, dim3(kWaves * 64), 0, st, a);
+    e = hipGetLastError();
+  } else {
     WsArgs wa;
     wa.s = a;
-    wa.k_splits = (int)k;
-    wa.sps = sps;
-    wa.part = nullptr;
-    if (k > 1) {
-      const size_t bytes = (size_t)k * (size_t)n_tokens * (size_t)h->rows * sizeof(float);
-      const int st_ok = ensure_spmm_part(h, bytes, st);
-      if (st_ok != SPDP_OK) return st_ok;
-      wa.part = static_cast<float*>(h->d_spmm_part);
-    }
-    const dim3 grid((unsigned)h->n_stripes, (unsigned)tiles, (unsigned)k);
-    if (wide)
+    wa.k_splits = plan.splits;
+    wa.sps = plan.per;
+    wa.part = part;
+    if (plan.form == kFormWs256)
       hipLaunchKernelGGL(spmm_ws256_kernel, grid, dim3(kW256Waves * 64), 0, st, wa);
     else
       hipLaunchKernelGGL(spmm_ws_kernel, grid, dim3(kWsWaves * 64), 0, st, wa);
-    if (k > 1) {
-      e = hipGetLastError();
-      if (e != hipSuccess) return hip_fail(e, "kernel launch");
-      const long long count = n_tokens * h->rows;
-      const long long per = (count & 3) == 0 ? count / 4 : count;
-      const unsigned blocks = (unsigned)std::min<long long>(8192, (per + 255) / 256);
-      hipLaunchKernelGGL(spmm_reduce_kernel, dim3(blocks), dim3(256), 0, st, wa.part, (int)k, count, Y);
-    }
-  } else {
-    hipLaunchKernelGGL(spmm_kernel, dim3((unsigned)h->n_stripes, (unsigned)tok_tiles), dim3(kWaves * 64), 0, st, a);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess) return hip_fail(e, "kernel launch");
+  if (plan.splits > 1) {
+    const long long count = n_tokens * h->rows;
+    const long long per = (count & 3) == 0 ? count / 4 : count;
+    const unsigned blocks = (unsigned)std::min<long long>(8192, (per + 255) / 256);
+    hipLaunchKernelGGL(spmm_reduce_kernel, dim3(blocks), dim3(256), 0, st, part, plan.splits, count, Y);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
