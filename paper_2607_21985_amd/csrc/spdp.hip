@@ -39,6 +39,9 @@
 //      the next call. No
 //      counter, no fence, no host-side state: a partial is usable as soon as
 //      its own store has landed, and a captured graph replays correctly.
+// Where the batch leaves few columns out (use_wide), launch_products runs the
+// all-columns form of wide.hip instead: steps 1-4 without a list, on word
+// records, the accumulate on the matrix cores; step 5 is the same.
 // With low-bit Values (spdp_encode_rtn, Sec. 5.1's quantization setup) the
 // same kernel reads one-byte codes: step 2 streams 16 codes per 16-byte
 // chunk, step 3 addresses bytes and turns each code into an fp16 integer

@@ -1019,11 +1019,11 @@ bool choose_spmm(const spdp_matrix* h, long long n_tokens, int cus, bool x_vec, 
 // The split-K partial sums of the prefill product: grown on demand, the
 // old buffer kept until the handle is freed (a captured graph may still
 // name it); no allocation while the stream is being captured. A growth also
-// covers what fewer tokens would take: the row form's
-// splits, and the warp-specialized rule's.
+// covers what fewer tokens would take: the row form's splits, and the
+// warp-specialized rule's.
 int ensure_spmm_part(spdp_matrix* h, int splits, int keep, long long n_tokens, hipStream_t stream) {
   const size_t row_bytes = (size_t)h->rows * sizeof(float);
-  if ((size_t)splits * (size_t)n_tokens * row_bytes <= h->spmm_part_bytes) return SPDP_OK;
+  if ((size_t)(splits > 1 ? splits : keep) * (size_t)n_tokens * row_bytes <= h->spmm_part_bytes) return SPDP_OK;
   size_t vectors = (size_t)std::max(splits, keep) * (size_t)n_tokens;
   if (h->d_rec)
     vectors = std::max(vectors, (size_t)std::min<long long>(row_max_splits(h) * n_tokens, row_part_tokens(h)));
@@ -1112,10 +1112,21 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
   if (!choose_spmm(h, n_tokens, cus, a.x_vec != 0, &plan))
     return fail(SPDP_ERR_UNSUPPORTED, "the width needs more than 65535 splits");
   float* part = nullptr;
-  if (plan.splits > 1) {
+  if (plan.splits > 1 || plan.keep > 1) {
     const int st_ok = ensure_spmm_part(h, plan.splits, plan.keep, n_tokens, st);
-    if (st_ok != SPDP_OK) return st_ok;
-    part = static_cast<float*>(h->d_spmm_part);
+    if (st_ok != SPDP_OK && plan.splits > 1) {
+      // No workspace (the stream is capturing, or no memory). The row form
+      // then runs with the splits that need no more than the
+      // warp-specialized rule would: one where that rule takes one (or none
+      // applies), else its own where they fit.
+      const bool rows = plan.form == kFormRows32 || plan.form == kFormRows64;
+      const bool fits = plan.keep == 1 || (size_t)plan.keep * (size_t)n_tokens * (size_t)h->rows * sizeof(float) <= h->spmm_part_bytes;
+      if (!rows || !fits) return st_ok;
+      plan.per = (h->chunks + plan.keep - 1) / plan.keep;
+      plan.splits = (h->chunks + plan.per - 1) / plan.per;
+    }
+    if (st_ok != SPDP_OK) (void)hipGetLastError();
+    if (plan.splits > 1) part = static_cast<float*>(h->d_spmm_part);
   }
   const dim3 grid((unsigned)h->n_stripes, (unsigned)plan.tiles, (unsigned)plan.splits);
   if (plan.form == kFormRows32 || plan.form == kFormRows64) {

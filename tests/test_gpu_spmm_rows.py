@@ -102,3 +102,27 @@ def test_a_call_covers_the_captures_of_fewer_tokens():
             assert torch.equal(y, Y[:n])
         del g
     m.close()
+
+
+@pytest.mark.parametrize("rows,cols,tile_k,n", [(512, 4093, 16, 33), (300, 2048, 32, 7), (40960, 264, 16, 128)])
+def test_a_first_call_inside_a_capture(rows, cols, tile_k, n):
+    # products that no split warp-specialized form serves (odd widths, other
+    # tile widths, more stripes than half the CUs) run unsplit where the
+    # stream is capturing and there is no workspace to split into
+    w, x = _inputs(rows, cols, n, 0.5, 9)
+    m = spdp.encode(w, (256, tile_k))
+    X = _to_dev(x)
+    y = torch.empty((n, rows), dtype=torch.float16, device=X.device)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        m.spmm_into(X, y)
+    want = m.spmm(X)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)  # dyadic inputs: the sums are exact in any order
+    del g
+    m.close()
