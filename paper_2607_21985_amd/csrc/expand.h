@@ -18,15 +18,14 @@
 
 #include <cstdint>
 
+#include "chunks.h"
+
 namespace spdp_dev {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGroupCols = 16;                         // columns of a record: the MFMA's k
-constexpr int kChunkGroups = 4;
-constexpr int kChunkCols = kGroupCols * kChunkGroups;  // columns staged between two barriers
 constexpr int kRecBytes = 160;
 constexpr int kChunkRecBytes = kChunkGroups * 4 * kRecBytes;
 

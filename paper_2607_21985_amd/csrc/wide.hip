@@ -141,9 +141,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
     uint32_t to = x0 + C::kWarm, off = extra_off;
     if (x_wave) {
       to = x0 + (uint32_t)((s & (kXAhead - 1)) * C::kXBytes + 1024 * wave);
-      // columns past the width: any valid 16 bytes (they are masked)
-      const int piece = (lane & 7) ^ (lane >> 3);
-      if ((c0 + s + 1) * kChunkCols > cols && (c0 + s) * kChunkCols + 8 * piece >= cols) off -= 16u * (uint32_t)piece;
+      off -= 16u * (uint32_t)pieces_back(c0 + s, (lane & 7) ^ (lane >> 3), cols);
     }
     dma16(extra, off, (uint32_t)__builtin_amdgcn_readfirstlane((int)to));
     extra_off += x_wave ? 2u * kChunkCols : (uint32_t)kChunkRecBytes;
@@ -446,7 +444,8 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
 
 // The word records of a matrix with 256-row tiles and tile_k >= 16: thread
 // (record, column) writes the column's word and offset. Columns past the
-// padded width (the last chunk's missing groups) get empty words.
+// padded width (the last chunk's missing groups) get empty words; padding
+// columns past the last chunk have no record.
 __global__ __launch_bounds__(256) void build_records_kernel(const uint32_t* tile_offset, const uint32_t* col_info,
                                                             const uint64_t* bitmap, const uint32_t* chunk_off,
                                                             int n_stripes, int n_colblocks, int tk_log2, int chunks,
@@ -539,8 +538,7 @@ int build_records(spdp_matrix* m) {
   using namespace spdp_dev;
   if (m->tile_m != 256 || m->tile_k < kGroupCols || m->value_bits != 16) return SPDP_OK;
   const int64_t per_tile = m->tile_k / kGroupCols;
-  const int64_t groups = m->n_colblocks * per_tile;
-  const int64_t chunks = (groups + kChunkGroups - 1) / kChunkGroups;
+  const int64_t chunks = chunk_count(m->cols);
   std::vector<uint32_t> off((size_t)(m->n_stripes * chunks + 1));
   uint32_t widest = 0;
   for (int64_t r = 0; r < m->n_stripes; ++r)
