@@ -225,14 +225,16 @@ int spdp_spmspv_many_mask(const spdp_handle_t* handles, int32_t count,
  * leaves compute units idle (few tokens), or when a stripe has more than
  * 1799 GTiles, the columns are split into k <= 16 ranges (more for very wide
  * matrices): one kernel writes k fp32 partial products into a workspace of
- * the handle (k * n_tokens * rows * 4 bytes; a growth also covers what calls
- * with fewer tokens take, at most 40 MB more than its own) and a second
+ * the handle (k * n_tokens * rows * 4 bytes) and a second
  * adds them in range order and rounds once to fp16. That workspace grows on
  * the first call that needs more (hipMalloc; the old one is kept until spdp_free,
- * so graphs captured earlier stay valid); growing it while `stream` is
- * being captured is refused with SPDP_ERR_INVALID_ARG (make one call with
- * at least as many tokens before the capture). SPDP_ERR_OOM if it cannot
- * be allocated. Calls on one handle that overlap in time on different
+ * so graphs captured earlier stay valid). The splits are not monotone in the
+ * token count: where a call splits, the workspace then also covers every call
+ * of fewer tokens (if memory allows; at most 68 MB in all on 256 compute
+ * units, or this call's own). Growing it while `stream` is
+ * being captured is refused with SPDP_ERR_INVALID_ARG (before the capture,
+ * make one call with the same token count, or one with more that splits).
+ * SPDP_ERR_OOM if it cannot be allocated. Calls on one handle that overlap in time on different
  * streams share the workspace and race. The fp32 summation order is fixed
  * by the matrix, the token count and the device's compute-unit count, so
  * equal inputs give equal bits on one device.

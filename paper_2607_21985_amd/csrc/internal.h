@@ -49,6 +49,7 @@ struct spdp_matrix {
   // Split-K partial sums of the prefill product (fp32, grown on demand).
   void* d_spmm_part = nullptr;
   size_t spmm_part_bytes = 0;
+  int64_t spmm_covered = 0;  // up to this token count the growth was asked to cover every call
   // Workspaces replaced by a larger one: a HIP graph captured earlier still
   // names them, so they live until the handle is freed.
   std::vector<void*> retired;

@@ -1016,33 +1016,75 @@ bool choose_spmm(const spdp_matrix* h, long long n_tokens, int cus, bool x_vec, 
   return plan->splits <= 65535;
 }
 
+// The rows of partials (fp32, one per output row) that any call of up to
+// n_tokens tokens takes: splits are not monotone in the token count (2048x8192:
+// 16 at 128 tokens, 4 at 511, 8 at 385), so the most over all counts, by
+// blocks of 32 tokens. Within one the warp-specialized rule's splits are
+// constant and the row form's do not rise (a split's cost rises with the
+// tokens); above `last` neither splits, but for the splits that a
+// TileOffset table forces on every count, which the last block has.
+long long spmm_cover(const spdp_matrix* h, long long n_tokens, int cus) {
+  int forced = 0;
+  if (const char* env = std::getenv("SPDP_SPMM_SPLITS")) forced = std::max(1, std::atoi(env));
+  const long long last = std::max<long long>(row_part_tokens(h), (long long)kBN256 * cus / h->n_stripes);
+  const long long end = (n_tokens - 1) / 32 * 32;
+  long long most = 0;
+  SpmmPlan p;
+  for (long long lo = 0; lo <= end; lo = lo < end && lo > last ? end : lo + 32) {
+    int splits = 1;
+    for (int tb = 1; tb <= 2 && h->d_rec != nullptr; ++tb) {
+      row_us(h, lo + 1, cus, tb, forced, &p);
+      splits = std::max(splits, p.splits);
+    }
+    if (h->tile_k == kKStep && h->cols % 8 == 0) {
+      ws_us(h, lo + 1, cus, 0, forced, &p);
+      splits = std::max(splits, p.splits);
+    }
+    if (splits > 1) most = std::max(most, splits * std::min(lo + 32, n_tokens));
+  }
+  return most;
+}
+
 // The split-K partial sums of the prefill product: grown on demand, the
 // old buffer kept until the handle is freed (a captured graph may still
 // name it); no allocation while the stream is being captured. A growth also
-// covers what fewer tokens would take: the row form's splits, and the
-// warp-specialized rule's.
-int ensure_spmm_part(spdp_matrix* h, int splits, int keep, long long n_tokens, hipStream_t stream) {
+// covers every call of fewer tokens; where there is no memory for that, only
+// this call (`own` rows of partials per token).
+int ensure_spmm_part(spdp_matrix* h, int own, long long n_tokens, int cus, hipStream_t stream) {
   const size_t row_bytes = (size_t)h->rows * sizeof(float);
-  if ((size_t)(splits > 1 ? splits : keep) * (size_t)n_tokens * row_bytes <= h->spmm_part_bytes) return SPDP_OK;
-  size_t vectors = (size_t)std::max(splits, keep) * (size_t)n_tokens;
-  if (h->d_rec)
-    vectors = std::max(vectors, (size_t)std::min<long long>(row_max_splits(h) * n_tokens, row_part_tokens(h)));
-  const size_t bytes = vectors * row_bytes;
+  const size_t own_bytes = (size_t)own * (size_t)n_tokens * row_bytes;
+  const bool fits = own_bytes <= h->spmm_part_bytes;
+  if (fits && n_tokens <= h->spmm_covered) return SPDP_OK;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(stream, &cs);
   if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
-  if (cs != hipStreamCaptureStatusNone)
+  if (cs != hipStreamCaptureStatusNone) {
+    if (fits) return SPDP_OK;
     return spdp::fail(SPDP_ERR_INVALID_ARG,
                       "the prefill split-K workspace is too small for this token count and the stream is "
-                      "capturing; call spdp_spmm once with at least as many tokens before the capture");
-  void* p = nullptr;
-  e = hipMalloc(&p, bytes);
-  if (e != hipSuccess)
-    return e == hipErrorOutOfMemory ? spdp::fail(SPDP_ERR_OOM, "hipMalloc of the prefill workspace failed")
-                                    : hip_fail(e, "hipMalloc");
-  if (h->d_spmm_part) h->retired.push_back(h->d_spmm_part);
-  h->d_spmm_part = p;
-  h->spmm_part_bytes = bytes;
+                      "capturing; call spdp_spmm once with this token count before the capture");
+  }
+  size_t bytes = std::max(own_bytes, (size_t)spmm_cover(h, n_tokens, cus) * row_bytes);
+  if (bytes > h->spmm_part_bytes) {
+    void* p = nullptr;
+    e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory && own_bytes < bytes) {
+      (void)hipGetLastError();
+      bytes = own_bytes;
+      e = fits ? hipSuccess : hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return e == hipErrorOutOfMemory ? spdp::fail(SPDP_ERR_OOM, "hipMalloc of the prefill workspace failed")
+                                      : hip_fail(e, "hipMalloc");
+    }
+    if (p) {
+      if (h->d_spmm_part) h->retired.push_back(h->d_spmm_part);
+      h->d_spmm_part = p;
+      h->spmm_part_bytes = bytes;
+    }
+  }
+  h->spmm_covered = std::max<long long>(h->spmm_covered, n_tokens);
   return SPDP_OK;
 }
 
@@ -1113,7 +1155,7 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
     return fail(SPDP_ERR_UNSUPPORTED, "the width needs more than 65535 splits");
   float* part = nullptr;
   if (plan.splits > 1 || plan.keep > 1) {
-    const int st_ok = ensure_spmm_part(h, plan.splits, plan.keep, n_tokens, st);
+    const int st_ok = ensure_spmm_part(h, plan.splits > 1 ? plan.splits : plan.keep, n_tokens, cus, st);
     if (st_ok != SPDP_OK && plan.splits > 1) {
       // No workspace (the stream is capturing, or no memory). The row form
       // then runs with the splits that need no more than the

@@ -16,11 +16,12 @@ struct Dim3 {
   uint32_t x, y, z;
 };
 
-std::map<const void*, std::string> g_names;
-std::map<void*, size_t> g_live;
+// never destroyed: handles may be freed while the process ends
+auto& g_names = *new std::map<const void*, std::string>;
+auto& g_live = *new std::map<void*, size_t>;
 size_t g_budget = ~size_t(0), g_used = 0;
 int g_capturing = 0, g_cus = 256, g_fail_attribute = 0;
-std::string g_log;  // one line a call: "malloc BYTES", "malloc-failed BYTES", "launch NAME X Y Z LDS"
+auto& g_log = *new std::string;  // one line a call: "malloc BYTES", "malloc-failed BYTES", "launch NAME X Y Z LDS"
 Dim3 g_grid, g_block;
 size_t g_shared;
 void* g_stream;

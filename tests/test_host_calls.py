@@ -60,3 +60,57 @@ int main() {
     subprocess.run([gxx, "-std=c++17", "-I", CSRC, str(src), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+SPMM_SIZES = [(2048, 8192, 16), (4096, 4096, 16), (512, 4093, 16), (300, 2048, 32), (5003, 3080, 16), (1024, 32768, 16)]
+
+
+@pytest.mark.parametrize("rows,cols,tile_k", SPMM_SIZES)
+def test_a_splitting_prefill_call_covers_every_capture_of_fewer_tokens(fake_hip, rows, cols, tile_k):
+    # sequences of calls, each growing the workspace or not, then a capture of
+    # any smaller count; the splits are not monotone in the token count
+    out = run(fake_hip, f"""
+    rng = np.random.default_rng(1)
+    refused = []
+    split = 0
+    sequences = [[128, 511], [32, 64], [16, 33, 200], [64, 333, 400]] + [
+        sorted(int(v) for v in np.exp(rng.uniform(0, np.log(1500), 3))) for _ in range(4)]
+    for seq in sequences:
+        m = ones({rows}, {cols}, (256, {tile_k}), 0.05)
+        for n in seq:
+            log()
+            assert spmm(m, n) == 0, (seq, n)
+        if any(k.startswith("18spmm_reduce") or "spmm_reduce" in k for k, _ in launches()):
+            split += 1
+            hip.fake_capturing(1)
+            for n in list(range(1, min(seq[-1], 300))) + list(range(300, seq[-1], 7)):
+                if spmm(m, n) != 0:
+                    refused.append([seq, n])
+            hip.fake_capturing(0)
+        m.close()
+    out["refused"], out["split"] = refused[:5], split
+    """)
+    assert out["split"] > 0 and not out["refused"], out
+
+
+def test_prefill_workspace_without_memory_for_more_than_the_call(fake_hip):
+    # room for this call's partials only: the call runs, and asks again for
+    # no more than it lacks
+    out = run(fake_hip, """
+    m = ones(2048, 8192, (256, 16), 0.05)
+    log()
+    assert spmm(m, 511) == 0
+    grid = [g for k, g in launches() if "spmm_rows" in k or "spmm_ws" in k][0]
+    m.close()
+    m = ones(2048, 8192, (256, 16), 0.05)
+    hip.fake_budget(hip.fake_used() + grid[2] * 511 * 2048 * 4)
+    log()
+    out["status"] = [spmm(m, 511) for _ in range(3)]
+    entries = log()
+    out["failed"] = sum(l[0] == "malloc-failed" for l in entries)
+    out["mallocs"] = sum(l[0] == "malloc" for l in entries)
+    out["error"] = L.spdp_last_error().decode()
+    m.close()
+    out["live"] = hip.fake_live()
+    """)
+    assert out == {"status": [0, 0, 0], "failed": 1, "mallocs": 1, "error": "", "live": 0}, out
