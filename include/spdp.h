@@ -231,10 +231,13 @@ int spdp_spmspv_many_mask(const spdp_handle_t* handles, int32_t count,
  * so graphs captured earlier stay valid). The splits are not monotone in the
  * token count: where a call splits, the workspace then also covers every call
  * of fewer tokens (if memory allows; at most 68 MB in all on 256 compute
- * units, or this call's own). Growing it while `stream` is
- * being captured is refused with SPDP_ERR_INVALID_ARG (before the capture,
- * make one call with the same token count, or one with more that splits).
- * SPDP_ERR_OOM if it cannot be allocated. Calls on one handle that overlap in time on different
+ * units, or this call's own). A call that finds no workspace, because
+ * `stream` is being captured or memory is short, adds its ranges in the
+ * kernel instead, in the same order (slower, the same bits), where tile_k is
+ * not 16, cols is not a multiple of 8 or the stripes are more than half the
+ * compute units; else it is refused with SPDP_ERR_INVALID_ARG (before the
+ * capture, make one call with the same token count, or one with more that
+ * splits) or SPDP_ERR_OOM. Calls on one handle that overlap in time on different
  * streams share the workspace and race. The fp32 summation order is fixed
  * by the matrix, the token count and the device's compute-unit count, so
  * equal inputs give equal bits on one device.

@@ -703,20 +703,18 @@ struct RowArgs {
   int slot;           // LDS bytes of a chunk's values (a multiple of 1024)
 };
 
-// XV: X rows are 16-byte aligned (else they are read by elements).
+// The sums of the chunks [c0, c0 + n) of a stripe. XV: X rows are 16-byte
+// aligned (else they are read by elements).
 template <int TB, bool XV>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TB == 1 ? 6 : 4))) void spmm_rows_kernel(RowArgs a) {
+__device__ __forceinline__ void rows_range(const RowArgs& a, unsigned char* lds, int c0, int n, float (&sum)[TB][16]) {
   using namespace spdp_dev;
   using C = RowCfg<TB>;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int word = wave & 3, half = wave >> 2;
   const int r = blockIdx.x;
   const long long nb0 = (long long)blockIdx.y * C::kTokens;
   const int last_tok = (int)min(a.n_tokens - nb0, (long long)C::kTokens) - 1;
-  const int c0 = (int)blockIdx.z * a.cps;
-  const int n = min(a.cps, a.chunks - c0);  // >= 1
   const uint32_t chunk0 = (uint32_t)r * (uint32_t)a.chunks + (uint32_t)c0;
   const uint32_t l0 = lds_addr(lds);
   const uint32_t slot = (uint32_t)a.slot;
@@ -827,7 +825,46 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TB == 1 ? 6
     for (int e = 0; e < 16; ++e)
       red[((wave * TB + j) * 16 + e) * 64 + lane] = half == 0 ? acc[1][j][e] : acc[0][j][e];
   __syncthreads();
-  const int row = r * kTM + 64 * word + 32 * half + (lane & 31);
+#pragma unroll
+  for (int j = 0; j < TB; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float other = red[(((wave ^ 4) * TB + j) * 16 + e) * 64 + lane];
+      sum[j][e] = half == 0 ? acc[0][j][e] + other : other + acc[1][j][e];
+    }
+}
+
+// FOLD: one workgroup walks all the ranges of cps chunks and adds their sums
+// in order in its registers; else grid.z workgroups write them to `part` for
+// spmm_reduce_kernel. The same sums in the same order, so the same bits, with
+// no workspace but on a smaller grid: for calls whose workspace cannot be had
+// (4096x4090 at 64 tokens 25.8 us split, 111 folded, 11008x4096 with 32-wide
+// tiles 30.6 and 96; the plain form takes 629 and 890).
+template <int TB, bool XV, bool FOLD>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((FOLD ? 4 : 6) - (TB == 1 ? 0 : 2)))) void spmm_rows_kernel(RowArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long nb0 = (long long)blockIdx.y * RowCfg<TB>::kTokens;
+  const int last_tok = (int)min(a.n_tokens - nb0, (long long)RowCfg<TB>::kTokens) - 1;
+  float sum[TB][16];
+  if constexpr (FOLD) {
+    rows_range<TB, XV>(a, lds, 0, min(a.cps, a.chunks), sum);
+    for (int c0 = a.cps; c0 < a.chunks; c0 += a.cps) {
+      __syncthreads();  // the range before has been read out of the LDS
+      float next[TB][16];
+      rows_range<TB, XV>(a, lds, c0, min(a.cps, a.chunks - c0), next);
+#pragma unroll
+      for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum[j][e] += next[j][e];
+    }
+  } else {
+    const int c0 = (int)blockIdx.z * a.cps;
+    rows_range<TB, XV>(a, lds, c0, min(a.cps, a.chunks - c0), sum);  // at least one chunk
+  }
+
+  const int row = (int)blockIdx.x * kTM + 64 * (wave & 3) + 32 * (wave >> 2) + (lane & 31);
   if (row >= a.rows) return;
   const bool split = gridDim.z > 1;
   float* const part = a.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows;
@@ -835,15 +872,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TB == 1 ? 6
   for (int j = 0; j < TB; ++j)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const float other = red[(((wave ^ 4) * TB + j) * 16 + e) * 64 + lane];
-      const float sum = half == 0 ? acc[0][j][e] + other : other + acc[1][j][e];
       const int t = 32 * j + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
       if (t > last_tok) continue;
       const size_t at = (size_t)(nb0 + t) * (size_t)a.rows + (size_t)row;
       if (split)
-        part[at] = sum;
+        part[at] = sum[j][e];
       else
-        a.y[at] = __half_as_ushort(__float2half_rn(sum));
+        a.y[at] = __half_as_ushort(__float2half_rn(sum[j][e]));
     }
 }
 
@@ -1088,10 +1123,10 @@ int ensure_spmm_part(spdp_matrix* h, int own, long long n_tokens, int cus, hipSt
   return SPDP_OK;
 }
 
-template <int TB, bool XV>
+template <int TB, bool XV, bool FOLD>
 hipError_t launch_rows_form(const RowArgs& a, dim3 grid, hipStream_t st) {
   const int lds = RowCfg<TB>::lds(a.slot);
-  const auto kernel = spmm_rows_kernel<TB, XV>;
+  const auto kernel = spmm_rows_kernel<TB, XV, FOLD>;
   if (lds > 64 * 1024) {
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1100,9 +1135,13 @@ hipError_t launch_rows_form(const RowArgs& a, dim3 grid, hipStream_t st) {
   hipLaunchKernelGGL(kernel, grid, dim3(512), lds, st, a);
   return hipGetLastError();
 }
-hipError_t launch_rows(const RowArgs& a, int tb, bool xv, dim3 grid, hipStream_t st) {
-  if (tb == 1) return xv ? launch_rows_form<1, true>(a, grid, st) : launch_rows_form<1, false>(a, grid, st);
-  return xv ? launch_rows_form<2, true>(a, grid, st) : launch_rows_form<2, false>(a, grid, st);
+template <int TB, bool XV>
+hipError_t launch_rows_fold(const RowArgs& a, bool fold, dim3 grid, hipStream_t st) {
+  return fold ? launch_rows_form<TB, XV, true>(a, grid, st) : launch_rows_form<TB, XV, false>(a, grid, st);
+}
+hipError_t launch_rows(const RowArgs& a, int tb, bool xv, bool fold, dim3 grid, hipStream_t st) {
+  if (tb == 1) return xv ? launch_rows_fold<1, true>(a, fold, grid, st) : launch_rows_fold<1, false>(a, fold, grid, st);
+  return xv ? launch_rows_fold<2, true>(a, fold, grid, st) : launch_rows_fold<2, false>(a, fold, grid, st);
 }
 
 }  // namespace
@@ -1154,23 +1193,22 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
   if (!choose_spmm(h, n_tokens, cus, a.x_vec != 0, &plan))
     return fail(SPDP_ERR_UNSUPPORTED, "the width needs more than 65535 splits");
   float* part = nullptr;
+  bool fold = false;
   if (plan.splits > 1 || plan.keep > 1) {
     const int st_ok = ensure_spmm_part(h, plan.splits > 1 ? plan.splits : plan.keep, n_tokens, cus, st);
     if (st_ok != SPDP_OK && plan.splits > 1) {
       // No workspace (the stream is capturing, or no memory). The row form
-      // then runs with the splits that need no more than the
-      // warp-specialized rule would: one where that rule takes one (or none
-      // applies), else its own where they fit.
+      // then folds its ranges in the kernel, where the warp-specialized rule
+      // asks for no more than there is: where it takes one split (or does
+      // not apply), or its splits fit.
       const bool rows = plan.form == kFormRows32 || plan.form == kFormRows64;
       const bool fits = plan.keep == 1 || (size_t)plan.keep * (size_t)n_tokens * (size_t)h->rows * sizeof(float) <= h->spmm_part_bytes;
       if (!rows || !fits) return st_ok;
-      plan.per = (h->chunks + plan.keep - 1) / plan.keep;
-      plan.splits = (h->chunks + plan.per - 1) / plan.per;
+      fold = true;
     }
-    if (st_ok != SPDP_OK) (void)hipGetLastError();
-    if (plan.splits > 1) part = static_cast<float*>(h->d_spmm_part);
+    if (plan.splits > 1 && !fold) part = static_cast<float*>(h->d_spmm_part);
   }
-  const dim3 grid((unsigned)h->n_stripes, (unsigned)plan.tiles, (unsigned)plan.splits);
+  const dim3 grid((unsigned)h->n_stripes, (unsigned)plan.tiles, fold ? 1u : (unsigned)plan.splits);
   if (plan.form == kFormRows32 || plan.form == kFormRows64) {
     RowArgs ra;
     std::memset(&ra, 0, sizeof(ra));
@@ -1186,7 +1224,7 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
     ra.chunks = h->chunks;
     ra.cps = plan.per;
     ra.slot = h->chunk_bytes;
-    e = launch_rows(ra, plan.form == kFormRows32 ? 1 : 2, a.x_vec != 0, grid, st);
+    e = launch_rows(ra, plan.form == kFormRows32 ? 1 : 2, a.x_vec != 0, fold, grid, st);
   } else if (plan.form == kFormPlain) {
     hipLaunchKernelGGL(spmm_kernel, grid, dim3(kWaves * 64), 0, st, a);
     e = hipGetLastError();
@@ -1203,7 +1241,7 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
     e = hipGetLastError();
   }
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
-  if (plan.splits > 1) {
+  if (part) {
     const long long count = n_tokens * h->rows;
     const long long per = (count & 3) == 0 ? count / 4 : count;
     const unsigned blocks = (unsigned)std::min<long long>(8192, (per + 255) / 256);

@@ -126,3 +126,35 @@ def test_a_first_call_inside_a_capture(rows, cols, tile_k, n):
         assert torch.equal(y, want)  # dyadic inputs: the sums are exact in any order
     del g
     m.close()
+
+
+@pytest.mark.parametrize("rows,cols,tile_k,n", [
+    (512, 4093, 16, 20),    # unaligned rows, 32 tokens a workgroup
+    (512, 4093, 16, 64),    # unaligned, 64
+    (300, 2048, 32, 7),     # aligned, 32, ragged rows
+    (300, 4096, 32, 150),   # aligned, several token tiles
+    (1000, 3000, 64, 64),
+    (40960, 264, 16, 128),  # more stripes than half the CUs
+])
+def test_a_call_without_workspace_gives_the_bits_of_the_others(rows, cols, tile_k, n):
+    # the first call inside a capture has no workspace to split into and folds
+    # its ranges in the kernel: the same sums in the same order
+    rng = np.random.default_rng(rows + n)
+    w = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.5)).astype(np.float16)
+    X = _to_dev(rng.standard_normal((n, cols)).astype(np.float16))
+    m = spdp.encode(w, (256, tile_k))
+    y = torch.empty((n, rows), dtype=torch.float16, device=X.device)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        m.spmm_into(X, y)
+    m.spmm(X[: max(1, n // 2)])
+    want = m.spmm(X)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+    del g
+    m.close()

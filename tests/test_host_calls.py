@@ -114,3 +114,31 @@ def test_prefill_workspace_without_memory_for_more_than_the_call(fake_hip):
     out["live"] = hip.fake_live()
     """)
     assert out == {"status": [0, 0, 0], "failed": 1, "mallocs": 1, "error": "", "live": 0}, out
+
+
+def test_prefill_without_workspace_keeps_its_ranges(fake_hip):
+    # inside a capture, and without memory, the row form walks the same ranges
+    # in one workgroup per stripe and token tile; what needed a workspace
+    # before that form existed is refused as it was
+    out = run(fake_hip, """
+    for rows, cols, tk, n in ((512, 4093, 16, 33), (300, 2048, 32, 7)):
+        m = ones(rows, cols, (256, tk), 0.05)
+        log()
+        hip.fake_capturing(1)
+        assert spmm(m, n) == 0
+        a = launches()
+        hip.fake_capturing(0)
+        hip.fake_budget(hip.fake_used())
+        assert spmm(m, n) == 0
+        b = launches()
+        hip.fake_budget((1 << 62))
+        assert spmm(m, n) == 0
+        c = launches()
+        out[f"same {rows}"] = a == b and len(a) == 1 and len(c) == 2 and a[0][1][:2] == c[0][1][:2]
+        out[f"split {rows}"] = a[0][1][2] == 1 and c[0][1][2] > 1
+        m.close()
+    m = ones(4096, 4096, (256, 16), 0.05)
+    hip.fake_capturing(1)
+    out["refused"] = spmm(m, 64) == -1
+    """)
+    assert all(out.values()), out
