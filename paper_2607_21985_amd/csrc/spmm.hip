@@ -1206,6 +1206,7 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
       if (!rows || !fits) return st_ok;
       fold = true;
     }
+    if (st_ok != SPDP_OK) spdp::clear_error();  // the call goes on without it
     if (plan.splits > 1 && !fold) part = static_cast<float*>(h->d_spmm_part);
   }
   const dim3 grid((unsigned)h->n_stripes, (unsigned)plan.tiles, fold ? 1u : (unsigned)plan.splits);

@@ -137,8 +137,13 @@ def test_prefill_without_workspace_keeps_its_ranges(fake_hip):
         out[f"same {rows}"] = a == b and len(a) == 1 and len(c) == 2 and a[0][1][:2] == c[0][1][:2]
         out[f"split {rows}"] = a[0][1][2] == 1 and c[0][1][2] > 1
         m.close()
-    m = ones(4096, 4096, (256, 16), 0.05)
+    # a call that succeeds leaves no message: folded, and unsplit where the
+    # older rule would have split
+    m = ones(512, 4093, (256, 16), 0.05)
     hip.fake_capturing(1)
+    out["folded"] = spmm(m, 33) == 0 and L.spdp_last_error() == b""
+    m = ones(4096, 4096, (256, 16), 0.05)
+    out["unsplit"] = all(spmm(m, n) != 0 or L.spdp_last_error() == b"" for n in range(1, 2200, 13))
     out["refused"] = spmm(m, 64) == -1
     """)
     assert all(out.values()), out
