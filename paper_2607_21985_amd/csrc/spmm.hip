@@ -1004,6 +1004,13 @@ float ws_us(const spdp_matrix* h, long long n_tokens, int cus, int form, int for
   return rounds * ((float)per * (wide ? 0.55f : 0.5f) + (wide ? 2.0f : 4.0f)) + split_us(plan->splits, n_tokens, h->rows);
 }
 
+// The forms that stage X by DMA address a token tile with 32-bit offsets: one
+// whose tile of X takes more than 4 GiB is left out (rows32 never does: a
+// handle has fewer than 2^26 columns).
+bool x_tile_fits(const spdp_matrix* h, long long n_tokens, int tile_tokens) {
+  return std::min<long long>(n_tokens, tile_tokens) * h->cols * 2 <= 1ll << 32;
+}
+
 // The form with the least modelled time. The row form needs the word
 // records, the warp-specialized ones 256 x 16 GTiles and a width that is a
 // multiple of 8; the plain one takes what is left. Measured, the
@@ -1031,7 +1038,8 @@ bool choose_spmm(const spdp_matrix* h, long long n_tokens, int cus, bool x_vec, 
     SpmmPlan p = *plan;
     const float us = ws_us(h, n_tokens, cus, form, forced, &p);
     p.keep = p.splits;
-    if (form != kFormRows32 && form != kFormRows64) {
+    const bool fits = x_tile_fits(h, n_tokens, p.form == kFormWs256 ? kBN256 : kBN);
+    if (fits && form != kFormRows32 && form != kFormRows64) {
       least = us;
       *plan = p;
     } else {
@@ -1041,6 +1049,7 @@ bool choose_spmm(const spdp_matrix* h, long long n_tokens, int cus, bool x_vec, 
   if (rows && !(ws && (form == kFormWs128 || form == kFormWs256)))
     for (int tb = 1; tb <= 2; ++tb) {
       if ((form == kFormRows32 && tb != 1) || (form == kFormRows64 && tb != 2)) continue;
+      if (!x_tile_fits(h, n_tokens, 32 * tb)) continue;
       SpmmPlan p = *plan;
       const float us = row_us(h, n_tokens, cus, tb, forced, &p);
       if (least < 0.0f || us < least) {

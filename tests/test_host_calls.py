@@ -147,3 +147,23 @@ def test_prefill_without_workspace_keeps_its_ranges(fake_hip):
     out["refused"] = spmm(m, 64) == -1
     """)
     assert all(out.values()), out
+
+
+@pytest.mark.slow
+def test_prefill_forms_address_their_tile_of_x_with_32_bits(fake_hip):
+    # 2^25 + 64 columns: the last token of a tile starts 2 (tokens - 1) cols
+    # bytes behind the first; the forms of 64, 128 and 256 tokens would wrap
+    out = run(fake_hip, """
+    cols = (1 << 25) + 64
+    w = np.zeros((1, cols), np.float16)
+    w[0, :100] = 1
+    m = spdp.encode(w, (256, 16))
+    del w
+    log()
+    for n in (20, 32, 33, 64, 129, 300):
+        assert spmm(m, n) == 0
+        k = launches()[0][0]
+        tile = 256 if "ws256" in k else 128 if "spmm_ws" in k else 64 if "ILi2E" in k else 32
+        out[f"{n}"] = min(n, tile) * cols * 2 <= 1 << 32
+    """)
+    assert len(out) == 6 and all(out.values()), out
