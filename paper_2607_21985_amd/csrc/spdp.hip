@@ -1477,7 +1477,6 @@ int finish_device(spdp_matrix* m, spdp_handle_t* out) {
   if (st == SPDP_OK) st = upload(m->bitmap, &m->d_bitmap);
   if (st == SPDP_OK) st = m->value_bits < 16 ? upload(m->codes, &m->d_values) : upload(m->values, &m->d_values);
   if (st == SPDP_OK && m->value_bits < 16) st = upload(m->scales, &m->d_scales);
-  if (st == SPDP_OK) st = spdp::build_records(m);
   if (st == SPDP_OK) {
     // every stripe starts in phase 1
     std::vector<uint32_t> ones((size_t)m->n_stripes, 1u);
@@ -1495,6 +1494,9 @@ int finish_device(spdp_matrix* m, spdp_handle_t* out) {
     choose_split(m, 1, &segments, &wave_cols, &passes);
     st = ensure_workspace(m, 1, segments, false, nullptr);
   }
+  // last, so that only memory that nothing else of the handle needs goes to
+  // the records (a handle works without them)
+  if (st == SPDP_OK) st = spdp::build_records(m);
   if (st != SPDP_OK) {
     release_device(m);
     delete m;

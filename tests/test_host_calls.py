@@ -167,3 +167,28 @@ def test_prefill_forms_address_their_tile_of_x_with_32_bits(fake_hip):
         out[f"{n}"] = min(n, tile) * cols * 2 <= 1 << 32
     """)
     assert len(out) == 6 and all(out.values()), out
+
+
+def test_encode_fits_where_the_handle_without_records_fits(fake_hip):
+    # the records take memory last and only what is left: every budget from
+    # the bare handle's on is enough, and its products run
+    out = run(fake_hip, """
+    log()
+    before = hip.fake_used()
+    m = ones(600, 2048, (256, 16), 0.3)
+    total = hip.fake_used() - before
+    records = 3 * (2048 // 64) * 2560 + 3 * 2560
+    assert records in [int(l[1]) for l in log() if l[0] == "malloc"]
+    m.close()
+    bare = total - records - (3 * 32 + 1) * 4 - 256
+    ok = []
+    for extra in [0, 100, 3000] + list(range(4096, records + 4096, 8192)):
+        hip.fake_budget(before + bare + extra)
+        m = ones(600, 2048, (256, 16), 0.3)
+        hip.fake_budget(1 << 62)
+        log()
+        ok.append(many([m], 8) == 0 and len(launches()) == 1)
+        m.close()
+    out["ok"], out["live"] = all(ok), hip.fake_live()
+    """)
+    assert out == {"ok": True, "live": 0}, out
