@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -534,9 +535,10 @@ int hip_fail(hipError_t e, const char* what) {
 
 namespace spdp {
 
-int build_records(spdp_matrix* m) {
+namespace {
+
+int lay_out_records(spdp_matrix* m) {
   using namespace spdp_dev;
-  if (m->tile_m != 256 || m->tile_k < kGroupCols || m->value_bits != 16) return SPDP_OK;
   const int64_t per_tile = m->tile_k / kGroupCols;
   const int64_t chunks = chunk_count(m->cols);
   std::vector<uint32_t> off((size_t)(m->n_stripes * chunks + 1));
@@ -589,6 +591,20 @@ int build_records(spdp_matrix* m) {
   m->chunks = (int)chunks;
   m->chunk_bytes = std::max(1024, (int)((widest + 1023) / 1024 * 1024));
   return SPDP_OK;
+}
+
+}  // namespace
+
+int build_records(spdp_matrix* m) {
+  if (m->tile_m != 256 || m->tile_k < spdp_dev::kGroupCols || m->value_bits != 16) return SPDP_OK;
+  try {
+    return lay_out_records(m);
+  } catch (const std::bad_alloc&) {  // no host memory for the offsets: no records
+    if (m->d_chunk_off) (void)hipFree(m->d_chunk_off);
+    if (m->d_rec) (void)hipFree(m->d_rec);
+    m->d_chunk_off = m->d_rec = nullptr;
+    return SPDP_OK;
+  }
 }
 
 }  // namespace spdp

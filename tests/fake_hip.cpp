@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 
 namespace {
@@ -19,7 +20,7 @@ struct Dim3 {
 // never destroyed: handles may be freed while the process ends
 auto& g_names = *new std::map<const void*, std::string>;
 auto& g_live = *new std::map<void*, size_t>;
-size_t g_budget = ~size_t(0), g_used = 0;
+size_t g_budget = ~size_t(0), g_used = 0, g_fail_new = 0;
 int g_capturing = 0, g_cus = 256, g_fail_attribute = 0;
 auto& g_log = *new std::string;  // one line a call: "malloc BYTES", "malloc-failed BYTES", "launch NAME X Y Z LDS"
 Dim3 g_grid, g_block;
@@ -38,6 +39,7 @@ void fake_budget(size_t bytes) { g_budget = bytes; }
 void fake_capturing(int on) { g_capturing = on; }
 void fake_cus(int n) { g_cus = n; }
 void fake_fail_attribute(int on) { g_fail_attribute = on; }
+void fake_fail_new(size_t bytes) { g_fail_new = bytes; }
 size_t fake_used() { return g_used; }
 size_t fake_live() { return g_live.size(); }
 const char* fake_log() { return g_log.c_str(); }
@@ -125,3 +127,13 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 
 }  // extern "C"
+
+// the library's host allocations, of which those of one size can be made to
+// fail
+void* operator new(size_t bytes) {
+  void* p = g_fail_new != 0 && bytes == g_fail_new ? nullptr : std::malloc(bytes ? bytes : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }

@@ -20,7 +20,7 @@ hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 hip.fake_log.restype = ctypes.c_char_p
 for f in (hip.fake_used, hip.fake_live):
     f.restype = ctypes.c_size_t
-hip.fake_budget.argtypes = [ctypes.c_size_t]
+hip.fake_budget.argtypes = hip.fake_fail_new.argtypes = [ctypes.c_size_t]
 import paper_2607_21985_amd as spdp
 L = spdp.lib()
 X, Y = 1 << 40, 1 << 44  # addresses that nothing reads

@@ -192,3 +192,21 @@ def test_encode_fits_where_the_handle_without_records_fits(fake_hip):
     out["ok"], out["live"] = all(ok), hip.fake_live()
     """)
     assert out == {"ok": True, "live": 0}, out
+
+
+def test_encode_without_host_memory_for_the_records(fake_hip):
+    # the records' chunk offsets are the only host array of their size: the
+    # handle comes without records, and no exception leaves the call
+    out = run(fake_hip, """
+    records = (3 * 32 + 3) * 2560
+    for fail in (0, (3 * 32 + 1) * 4):
+        log()
+        hip.fake_fail_new(fail)
+        m = ones(600, 2048, (256, 16), 0.3)
+        hip.fake_fail_new(0)
+        out[f"{fail}"] = records in [int(l[1]) for l in log() if l[0] == "malloc"]
+        assert many([m], 8) == 0 and spmm(m, 64) == 0
+        m.close()
+    out["live"] = hip.fake_live()
+    """)
+    assert out == {"0": True, "388": False, "live": 0}, out
