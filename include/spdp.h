@@ -95,15 +95,20 @@ int spdp_encode_host(const uint16_t* W, int64_t rows, int64_t cols,
  *              column k takes part for token b iff |X[b,k]| > threshold
  *              (strict). A negative threshold keeps every column; NaN is
  *              SPDP_ERR_INVALID_ARG. NaN activations are never active.
- *              Columns inactive for every token of the batch take no part
- *              (with several tokens, where nearly every column is active for
- *              some token, they may be read and multiplied by 0).
+ *              Columns inactive for every token of the batch take no part.
+ *              They are not read with up to 4 tokens. With more, a small
+ *              matrix (up to 20 million weights; 27 from 8 tokens, 100 from
+ *              17) is read whole whatever the threshold, and inactive columns
+ *              are multiplied by 0; a larger one is read whole if, in a sample
+ *              of X, so many columns are active for some token (30 to 75 % by
+ *              size and batch) that this is faster.
  *   Y          device, batch x rows fp16, row-major, fully overwritten with
  *              the fp32-accumulated result rounded once to nearest even.
  *              Must not overlap X.
  *   stream     hipStream_t to enqueue on (NULL = the null stream).
  *
- * Asynchronous: the call validates, enqueues one kernel and returns; X and Y
+ * Asynchronous: the call validates, enqueues one kernel (two where it samples
+ * X: one that leaves the product to the other) and returns; X and Y
  * must stay valid until the stream passes the work. The handle's workspace
  * is reused by every call, so one handle must not run on two streams at
  * once. The first call with a larger batch than before grows the workspace:

@@ -24,4 +24,17 @@ constexpr int pieces_back(int chunk, int piece, int cols) {
   return (chunk + 1) * kChunkCols > cols && chunk * kChunkCols + 8 * piece >= cols ? piece : 0;
 }
 
+// The sample of the activations by which a gated call picks its form: four
+// chunks spread over the width (the middles of its quarters), every token.
+constexpr int kSampleChunks = 4;
+constexpr int sample_chunk(int j, int chunks) { return (int)((2 * (int64_t)j + 1) * chunks / (2 * kSampleChunks)); }
+constexpr int sample_columns(int chunks, int cols) {
+  int n = 0;
+  for (int j = 0; j < kSampleChunks; ++j) {
+    const int left = cols - sample_chunk(j, chunks) * kChunkCols;
+    n += left < kChunkCols ? left : kChunkCols;
+  }
+  return n;
+}
+
 }  // namespace spdp_dev

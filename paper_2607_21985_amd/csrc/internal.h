@@ -36,6 +36,7 @@ struct spdp_matrix {
   // fp16 values with 256-row tiles and tile_k >= 16, else NULL.
   void* d_rec = nullptr;
   void* d_chunk_off = nullptr;
+  uint32_t* d_gate = nullptr;  // what a gated call decided (launch.h), behind the offsets
   int chunks = 0;       // chunks (64 columns) of a stripe: those that hold a column below cols
   int chunk_bytes = 0;  // LDS bytes that hold any chunk's values
   bool finite = true;   // no infinity or NaN among the values (set with the records)

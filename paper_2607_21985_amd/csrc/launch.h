@@ -13,7 +13,13 @@ struct MatArgs {
   const uint32_t* col_info;
   const uint64_t* bitmap;
   const uint16_t* values;  // fp16 values, or one-byte codes (the kernel's Q form)
-  const float* scales;     // Q form: one scale per row
+  union {
+    const float* scales;   // Q form: one scale per row
+    // fp16 values: NULL, or the product's gate, a word that a launch of the
+    // all-columns form has written before (wide.hip): not 0 where that launch
+    // has done the product, which this one then leaves out
+    const uint32_t* gate;
+  };
   const uint16_t* x;
   uint16_t* y;
   // [segments][batch][n_stripes * tile_m]: {fp32 bits, phase} pairs
@@ -45,12 +51,6 @@ struct MatArgs {
   float batch_thr;
   // consecutive K ranges (of kWaves x wave_cols columns) per workgroup
   int passes;
-  // the all-columns form (wide.hip): the word records, the chunks' value
-  // offsets, the stripe's chunks and the chunks of one segment
-  const unsigned char* rec;
-  const uint32_t* chunk_off;
-  int chunks;
-  int seg_chunks;
 };
 
 // A launch runs up to kMaxGroup independent products (same tile height and
@@ -61,10 +61,40 @@ constexpr int kMaxGroup = 8;
 struct LaunchArgs {
   MatArgs m[kMaxGroup];
   int batch;
-  int slot;  // all-columns form: LDS bytes of a chunk's values, the most of the launch's products
 };
 
+// One product of an all-columns launch (wide.hip). Where a field's name is
+// one of MatArgs, it means the same; segments and n_wg are this form's own.
+struct WideArgs {
+  const unsigned char* rec;   // word records, [stripe][chunk]
+  const uint32_t* chunk_off;  // the chunks' value offsets
+  const uint16_t* values;
+  const uint16_t* x;
+  uint16_t* y;
+  unsigned long long* partials;
+  uint32_t* phase;
+  uint32_t* epoch_done;
+  // NULL: every column takes part whatever the activations. Else the form
+  // runs only if at least gate_min columns of a sample of the activations are
+  // active for some token; the word tells the per-column launch that follows
+  uint32_t* gate;
+  int gate_min;
+  int phase_step;
+  int rows, cols;
+  int n_stripes;
+  int code;
+  int segments;
+  int n_wg;
+  float batch_thr;
+  int chunks;      // chunks of a stripe
+  int seg_chunks;  // chunks of a segment
+};
 
-// Launches the all-columns form (wide.hip) for `batch` tokens: the grid's
-// workgroups are those of the per-column kernels.
-hipError_t launch_wide(const LaunchArgs& args, int count, bool bmask, dim3 grid, hipStream_t stream);
+struct WideLaunch {
+  WideArgs m[kMaxGroup];
+  int batch;
+  int slot;  // LDS bytes of a chunk's values, the most of the launch's products
+};
+
+// Launches the all-columns form for `batch` tokens.
+hipError_t launch_wide(const WideLaunch& args, int count, bool bmask, dim3 grid, hipStream_t stream);

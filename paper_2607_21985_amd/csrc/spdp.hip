@@ -39,9 +39,9 @@
 //      the next call. No
 //      counter, no fence, no host-side state: a partial is usable as soon as
 //      its own store has landed, and a captured graph replays correctly.
-// Where the batch leaves few columns out (use_wide), launch_products runs the
-// all-columns form of wide.hip instead: steps 1-4 without a list, on word
-// records, the accumulate on the matrix cores; step 5 is the same.
+// From 5 tokens on, launch_products may run the all-columns form of wide.hip
+// instead, or ahead as a gate (choose_route): steps 1-4 without a list, on
+// word records, the accumulate on the matrix cores; step 5 is the same.
 // With low-bit Values (spdp_encode_rtn, Sec. 5.1's quantization setup) the
 // same kernel reads one-byte codes: step 2 streams 16 codes per 16-byte
 // chunk, step 3 addresses bytes and turns each code into an fp16 integer
@@ -52,12 +52,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
 #include <string>
 
+#include "chunks.h"
 #include "internal.h"
 #include "launch.h"
 
@@ -346,10 +348,16 @@ __device__ __forceinline__ void spmspv_body() {
   const void* const values = A->values;
   const void* const bitmap = A->bitmap;
   const uint32_t zero_col = A->zero_col;
+  // the calls that can be gated: per-token masks, 5 or more tokens, fp16
+  // values, 256-row tiles
+  constexpr bool kGated = NB >= 8 && WPC == 4 && !BMASK && !Q && !MM;
+  const const_ptr<uint32_t> gate_p = kGated ? (const_ptr<uint32_t>)A->gate : nullptr;
   asm volatile("" ::"s"(n_seg0), "s"(batch), "s"(tk_log2), "s"(n_colblocks), "s"(code), "s"(cols),
                "s"(wave_cols), "s"(phase_p), "s"(col_info_p), "s"(tile_offset_p), "s"(x_p), "s"(values),
                "s"(bitmap), "s"(zero_col), "s"(early_first), "s"(batch_thr));
   if (local >= n_wg) return;  // the whole workgroup: no barrier has been reached
+  if constexpr (kGated)
+    if (gate_p != nullptr && *gate_p != 0) return;  // the all-columns launch before has done the product
   const int r = (int)(local / n_seg0);
   const int seg = (int)(local - (uint32_t)r * n_seg0);
   const int tk_mask = (1 << tk_log2) - 1;
@@ -1300,37 +1308,74 @@ int early_first(int batch, int64_t workgroups) {
   return workgroups <= kEarlyFirstMaxWorkgroups ? 1 : 0;
 }
 
-// The all-columns form (wide.hip) serves fp16 values in 256-row tiles
-// (records exist) where the columns that the batch leaves out cost less than
-// finding them. Measured at 0, 50 and 70 % activation sparsity, per-column ->
-// all-columns, us:
-//   per-token masks (at 70 % the union of 8 tokens has 94 % of the columns):
-//     8 tokens: 4096x4096 18.6 -> 12.4 (three grouped 37.0-38.2 -> 20.6),
-//     11008x4096 (two) 38.7-39.8 -> 35, 5120x13824 33.5-34.2 -> 25.7,
-//     28672x8192 69.0-73.8 -> 66.8; 16 and 32 tokens gain more (28672x8192 at
-//     32: 154 -> 85);
-//     5 tokens: 4096x4096 16.5-17.2 -> 11.9, 5120x13824 29.9-32.5 -> 25.4,
-//     11008x4096 (two) 32.8-36.5 -> 32.5, but 28672x8192 at 70 % 59.2 -> 65.6;
-//     4 tokens: 4096x4096 13.5-14.2 -> 11.8, 1024x8192 (three) 17.0-18.8 ->
-//     16.4, but 5120x13824 at 70 % 24.6 -> 25.5;
-//   one mask for the batch (25, 50 and 70 %): 8 and 16 tokens 4096x4096
-//     14.5-17.6 -> 13.6 and 17.0-19.7 -> 16.1, three grouped 28.8-35.2 -> 21.7
-//     and 36.2-45.5 -> 26.1; larger products lose (28672x8192 44.8 -> 71.7),
-//     and so do three grouped above 16 tokens, where every workgroup sums
-//     all tokens' scores (1792x1600 at 25 % and 25 tokens 20.7 -> 22.9,
-//     4096x4096 at 70 % and 32 43.7 -> 46.5).
-// A matrix with infinities or NaNs stays with the per-column kernels, which
-// do not multiply a column that no token has active. A property of the
-// matrix, the batch and the mask, so a product gives the same bits alone and
+// The form of a product with several tokens. The all-columns form (wide.hip)
+// serves fp16 values in 256-row tiles (records exist) without infinities and
+// NaNs (the per-column kernels do not multiply a column that no token has
+// active); its time does not depend on the activations. That of the
+// per-column kernels falls with the share u of columns that are active for
+// some token, which only the activations tell: 1 - p^batch where tokens drop
+// the share p independently, 1 - p where they drop the same columns.
+// Measured (70 % weight sparsity, us), per-column at u = 1 / 0.5 / 0.1 against
+// all-columns:
+//   per-token masks, 5 tokens: 4096x4096 17.8 / 15.4 / 13.3 - 11.1, three
+//     grouped 31.0 / 26.3 / 26.0 - 19.4, 8192x2048 15.4 / 12.6 / 10.6 - 11.0;
+//     8 tokens: 21.0 / 18.3 / 16.9 - 11.5 and 33.7 / 29.6 / 29.4 - 19.9,
+//     5120x5120 22.0 / 18.0 / 15.8 - 15.1, three 34.6 / 26.9 / 23.7 - 27.2 (a
+//     gate, below, would cost as much as it saves at u = 0.1); 17 tokens:
+//     11008x4096 38.6 / 30.0 / 23.3 - 23.4, two 13824x5120 105.0 / 78.4 / 55.3
+//     - 51.3, at 32 8192x8192 67.4 / 50.7 / 35.4 - 33.8;
+//     up to 20 million weights, 27 from 8 tokens and 100 from 17 it wins
+//     whatever the activations, so it always runs; with 4 tokens it loses where the columns are few (three 4096x4096
+//     23.1 / 18.2 / 19.6 - 19.2, and 16.5 at u = 0.3), and with 5 to 8 where
+//     the stripes are many and short (16384x1024 at 5 14.0 / 11.3 / 9.3 -
+//     11.8, 28000x700 at 8 14.7 / 12.7 / 11.0 - 17.4);
+//   other products win or lose by u: at 8 tokens 5120x13824 34.3 / 25.0 /
+//     20.0 - 26.2, 8192x8192 30.8 / 22.3 / 16.7 - 23.5, 8192x28672 72.8 / 46.7
+//     / 24.4 - 57.2, at 32 28672x8192 153.9 / 104.1 / 62.7 - 82.2. Such calls
+//     are gated: the all-columns launch looks at a sample of the activations
+//     and leaves the product to a per-column launch behind it where too few
+//     columns are active. That costs 2 us where it runs and 3 to 4 where it
+//     does not (5120x13824 at 8 tokens 28.2 and 23.1 at u = 1 and 0.1), so
+//     products that gain no more stay per-column (28672x8192 at 8 tokens 68.8
+//     - 64.5, two grouped 116.6 - 122.5). With a negative threshold every
+//     column takes part and no gate is needed.
+//   one mask for the batch: 8 and 16 tokens 4096x4096 21.2 / 18.3 / 16.7 -
+//     12.6 and 25.9 / 23.1 / 21.6 - 15.7, three grouped 34.3 / 29.2 / 29.2 -
+//     20.6 and 39.2 / 35.8 / 33.6 - 24.5; larger products lose at the shares
+//     that such masks leave, and so do three grouped above 16 tokens, where
+//     every workgroup sums all tokens' scores (1792x1600 at 25 % and 25
+//     tokens 20.7 - 22.9).
+// A property of the matrix, the batch,
+// the mask and the activations, so a product gives the same bits alone and
 // grouped. SPDP_WIDE overrides the token count from which the form runs (0:
-// never; for tuning).
-constexpr int64_t kWideSmall = 20000000, kWideMedium = 100000000;  // weights, the zeros included
-bool use_wide(const spdp_matrix* h, int batch, bool bmask) {
-  if (!h->d_rec || !h->finite || batch < 2 || use_mfma(batch)) return false;
-  if (const char* env = std::getenv("SPDP_WIDE")) return std::atoi(env) > 0 && batch >= std::atoi(env);
+// never; -n: gated from n tokens, at least 5; for tuning).
+enum Route { kPerColumn, kAllColumns, kGated };
+constexpr int64_t kWideMedium = 100000000;  // weights, the zeros included
+Route choose_route(const spdp_matrix* h, int batch, bool bmask, int32_t code) {
+  if (!h->d_rec || !h->finite || batch < 2 || use_mfma(batch)) return kPerColumn;
+  if (const char* env = std::getenv("SPDP_WIDE")) {
+    const int from = std::atoi(env);
+    if (from < 0) return !bmask && batch >= std::max(5, -from) ? kGated : kPerColumn;
+    return from > 0 && batch >= from ? kAllColumns : kPerColumn;
+  }
   const int64_t weights = h->rows * h->cols;
-  if (bmask) return batch >= 8 && batch <= 16 && weights <= kWideSmall;
-  return batch >= (weights <= kWideSmall ? 4 : weights <= kWideMedium ? 5 : 8);
+  const bool small = weights <= (batch < 8 || bmask ? 20000000 : 27000000);
+  if (bmask) return small && batch >= 8 && batch <= 16 ? kAllColumns : kPerColumn;
+  if (batch < 5) return kPerColumn;
+  if (small) return batch <= 8 && h->rows > 8 * h->cols ? kPerColumn : kAllColumns;
+  if (batch > 16 && weights <= kWideMedium) return kAllColumns;
+  if (weights > kWideMedium && batch <= 8 && (batch < 8 || h->rows > h->cols)) return kPerColumn;
+  return code < 0 ? kAllColumns : kGated;
+}
+
+// The share of the sample's columns from which a gated product runs in the
+// all-columns form: about where the two tie (at 8 tokens u = 0.56 to 0.7; at
+// 16 0.5 to 0.6, but 0.8 with many rows, 11008x4096 and 28672x8192 grouped;
+// at 32 up to 0.34).
+float gate_share(const spdp_matrix* h, int batch) {
+  if (batch <= 8) return 0.7f;
+  if (batch <= 16) return h->rows > 2 * h->cols ? 0.75f : 0.5f;
+  return 0.3f;
 }
 
 // Chunks (64 columns) per segment of the all-columns form: at most `segments`
@@ -1373,7 +1418,7 @@ struct SharedWorkspace {
 // Validates one product of a call and fills its kernel arguments: with the
 // handle's workspace (sized for the batch if needed), or with `shared`.
 int prepare(spdp_handle_t h, const uint16_t* X, int32_t batch, float threshold, int32_t mask, uint16_t* Y, int dev,
-            hipStream_t stream, const SharedWorkspace* shared, MatArgs* out, int64_t* n_wg, bool* wide) {
+            hipStream_t stream, const SharedWorkspace* shared, MatArgs* out, Route* route) {
   if (!h) return fail(SPDP_ERR_INVALID_ARG, "handle is NULL");
   if (h->device < 0) return fail(SPDP_ERR_INVALID_ARG, "handle has no device copy");
   if (!X || !Y) return fail(SPDP_ERR_INVALID_ARG, "X or Y is NULL");
@@ -1409,7 +1454,10 @@ int prepare(spdp_handle_t h, const uint16_t* X, int32_t batch, float threshold, 
   a.col_info = static_cast<const uint32_t*>(h->d_col_info);
   a.bitmap = static_cast<const uint64_t*>(h->d_bitmap);
   a.values = static_cast<const uint16_t*>(h->d_values);
-  a.scales = static_cast<const float*>(h->d_scales);
+  if (h->value_bits < 16)
+    a.scales = static_cast<const float*>(h->d_scales);
+  else
+    a.gate = nullptr;
   a.x = X;
   a.y = Y;
   a.partials = shared ? shared->partials : h->d_partials;
@@ -1427,21 +1475,39 @@ int prepare(spdp_handle_t h, const uint16_t* X, int32_t batch, float threshold, 
   a.wave_cols = wave_cols;
   a.segments = segments;
   a.passes = passes;
-  *n_wg = (int64_t)segments * h->n_stripes;
-  a.n_wg = (int)*n_wg;
-  a.early_first = early_first(batch, *n_wg);
-  a.rec = static_cast<const unsigned char*>(h->d_rec);
-  a.chunk_off = static_cast<const uint32_t*>(h->d_chunk_off);
-  a.chunks = h->chunks;
-  *wide = use_wide(h, batch, mask == SPDP_MASK_BATCH && batch > 1);
-  if (*wide) {
-    a.seg_chunks = wide_seg_chunks(h, batch, segments);
-    a.segments = (h->chunks + a.seg_chunks - 1) / a.seg_chunks;
-    *n_wg = (int64_t)a.segments * h->n_stripes;
-    a.n_wg = (int)*n_wg;
-  }
+  const int64_t n_wg = (int64_t)segments * h->n_stripes;
+  if (n_wg >= (int64_t(1) << 31)) return fail(SPDP_ERR_UNSUPPORTED, "more than 2^31 - 1 workgroups");
+  a.n_wg = (int)n_wg;
+  a.early_first = early_first(batch, n_wg);
+  *route = choose_route(h, batch, mask == SPDP_MASK_BATCH && batch > 1, code);
+  if (*route == kGated) a.gate = h->d_gate;
   a.batch_thr = mask == SPDP_MASK_BATCH ? (float)((double)threshold * (double)batch) : 0.0f;
   return SPDP_OK;
+}
+
+// The same product's arguments for the all-columns form.
+void prepare_wide(const spdp_matrix* h, const MatArgs& a, int batch, Route route, WideArgs* out) {
+  WideArgs& w = *out;
+  w.rec = static_cast<const unsigned char*>(h->d_rec);
+  w.chunk_off = static_cast<const uint32_t*>(h->d_chunk_off);
+  w.values = a.values;
+  w.x = a.x;
+  w.y = a.y;
+  w.partials = a.partials;
+  w.phase = a.phase;
+  w.epoch_done = a.epoch_done;
+  w.gate = route == kGated ? h->d_gate : nullptr;
+  w.gate_min = (int)std::ceil(gate_share(h, batch) * (float)spdp_dev::sample_columns(h->chunks, a.cols));
+  w.phase_step = a.phase_step;
+  w.rows = a.rows;
+  w.cols = a.cols;
+  w.n_stripes = a.n_stripes;
+  w.code = a.code;
+  w.batch_thr = a.batch_thr;
+  w.chunks = h->chunks;
+  w.seg_chunks = wide_seg_chunks(h, batch, a.segments);
+  w.segments = (h->chunks + w.seg_chunks - 1) / w.seg_chunks;
+  w.n_wg = (int)(w.segments * h->n_stripes);
 }
 
 bool overlap(const void* p, size_t pn, const void* q, size_t qn) {
@@ -1535,48 +1601,45 @@ int launch_products(const spdp_handle_t* handles, int32_t count, const uint16_t*
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  // [0]: the per-column kernels' products, [1]: the all-columns form's
-  LaunchArgs args[2];
-  int counts[2] = {0, 0};
-  int64_t widest[2] = {0, 0};
-  std::memset(args, 0, sizeof(args));
-  args[0].batch = args[1].batch = batch;
+  LaunchArgs la;  // the per-column kernels' products
+  WideLaunch wl;  // the all-columns form's; a gated product is in both
+  int n_la = 0, n_wl = 0, widest = 0, widest_wl = 0;
+  la.batch = wl.batch = batch;
+  wl.slot = 0;
   bool early = false, multi = false, wide = false;
   const bool bmask = mask == SPDP_MASK_BATCH && batch > 1;
   for (int i = 0; i < count; ++i) {
-    int64_t n_wg = 0;
-    bool all_columns = false;
-    MatArgs m;
-    std::memset(&m, 0, sizeof(m));
+    MatArgs& m = la.m[n_la];
+    Route route = kPerColumn;
     const int st = prepare(handles[i], X[i], batch, thresholds[i], mask, Y[i], dev, static_cast<hipStream_t>(stream),
-                           shared, &m, &n_wg, &all_columns);
+                           shared, &m, &route);
     if (st != SPDP_OK) return st;
     if (handles[i]->tile_m != handles[0]->tile_m)
       return fail(SPDP_ERR_INVALID_ARG, "the matrices of one call must share tile_m");
     if ((handles[i]->value_bits < 16) != (handles[0]->value_bits < 16))
       return fail(SPDP_ERR_INVALID_ARG, "the matrices of one call must all hold fp16 values or all codes");
-    if (n_wg >= (int64_t(1) << 31)) return fail(SPDP_ERR_UNSUPPORTED, "more than 2^31 - 1 workgroups");
-    const int k = all_columns ? 1 : 0;
-    args[k].m[counts[k]++] = m;
-    widest[k] = std::max(widest[k], n_wg);
-    if (all_columns) {
-      args[1].slot = std::max(args[1].slot, handles[i]->chunk_bytes);
-    } else {
+    if (route != kPerColumn) {
+      prepare_wide(handles[i], m, batch, route, &wl.m[n_wl]);
+      wl.slot = std::max(wl.slot, handles[i]->chunk_bytes);
+      widest_wl = std::max(widest_wl, wl.m[n_wl].n_wg);
+      ++n_wl;
+    }
+    if (route != kAllColumns) {
+      widest = std::max(widest, m.n_wg);
       early = early || m.early_first;
       multi = multi || m.passes > 1;
       wide = wide || m.wave_cols > kNarrowWaveCols;
+      ++n_la;
     }
   }
-  if (counts[1] > 0) {
-    e = launch_wide(args[1], counts[1], bmask, dim3((unsigned)widest[1], (unsigned)counts[1]),
-                    static_cast<hipStream_t>(stream));
+  if (n_wl > 0) {
+    e = launch_wide(wl, n_wl, bmask, dim3((unsigned)widest_wl, (unsigned)n_wl), static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
-    if (counts[0] == 0) return SPDP_OK;
+    if (n_la == 0) return SPDP_OK;
   }
-  const LaunchArgs& la = args[0];
 
   const int wpc = handles[0]->tile_m / 64;
-  const dim3 grid((unsigned)widest[0], (unsigned)counts[0]);
+  const dim3 grid((unsigned)widest, (unsigned)n_la);
   const bool q = handles[0]->value_bits < 16;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool mm = use_mfma(batch);

@@ -1,12 +1,19 @@
-// Decode in which every column takes part (the all-columns form): batches
-// whose tokens' active columns, taken together, are nearly all columns. A
-// column that no token has active is then multiplied by zeros instead of
-// being skipped, and the values stream as contiguous runs, with no list of
-// columns, into the expansion of expand.h and 32x32x16 MFMAs.
+// Decode in which every column takes part (the all-columns form): for batches
+// whose tokens' active columns, taken together, are nearly all columns, and
+// for products so small that finding them costs more than they do
+// (choose_route in spdp.hip). A column that no token has active is then
+// multiplied by zeros instead of being skipped, and the values stream as
+// contiguous runs, with no list of columns, into the expansion of expand.h
+// and 32x32x16 MFMAs.
 //
-// Grid, segments and the split-K exchange are those of the per-column kernels
-// (spdp.hip): workgroup x is stripe x / segments, segment x mod segments, of
-// product blockIdx.y. Eight waves: wave w expands bitmap word w mod 4 (64
+// A gated launch finds out for itself: each workgroup first counts, over four
+// chunks of the activations, the columns that some token has active, and
+// leaves if they are too few; a word tells the per-column launch behind it.
+//
+// The grid is the per-column kernels' in shape (workgroup x is stripe
+// x / segments, segment x mod segments, of product blockIdx.y; the segments
+// are this form's own, wide_seg_chunks), and so is the split-K exchange. Eight
+// waves: wave w expands bitmap word w mod 4 (64
 // rows) of the groups 2 (w / 4), 2 (w / 4) + 1 of every chunk (64 columns)
 // and multiplies them with all tokens; the two halves of the chunk are added
 // once, at the end.
@@ -82,7 +89,7 @@ __device__ __forceinline__ void wait_barrier() {
 // are not 16-byte aligned are read by elements, and every wait is for all
 // loads).
 template <int NT, bool BMASK, int NP>
-__global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6))) void wide_kernel(LaunchArgs) {
+__global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6))) void wide_kernel(WideLaunch) {
   using C = WideCfg<NT>;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
@@ -90,8 +97,8 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
   const int word = wave & 3;
   const int half = wave >> 2;
 
-  const const_ptr<LaunchArgs> L = (const_ptr<LaunchArgs>)__builtin_amdgcn_kernarg_segment_ptr();
-  const const_ptr<MatArgs> A = &L->m[blockIdx.y];
+  const const_ptr<WideLaunch> L = (const_ptr<WideLaunch>)__builtin_amdgcn_kernarg_segment_ptr();
+  const const_ptr<WideArgs> A = &L->m[blockIdx.y];
   const uint32_t local = blockIdx.x;
   const uint32_t n_seg0 = (uint32_t)A->segments;
   if (local >= (uint32_t)A->n_wg) return;  // the whole workgroup: no barrier has been reached
@@ -111,7 +118,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
   const uint32_t slot = (uint32_t)L->slot;
   const uint32_t x0 = l0 + 2 * slot;
 
-  // Loads. Every chunk, a wave requests NP kilobytes of values (two chunks
+  // Loads. Every chunk, a wave requests NP kilobytes of values (one chunk
   // ahead) and one more kilobyte: wave w < NT / 8 eight tokens' activations
   // (four chunks ahead), the others records, into L2 (they land where nobody
   // reads).
@@ -121,8 +128,10 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
   const unsigned char* const extra =
       x_wave ? (const unsigned char*)(A->x + (size_t)c0 * kChunkCols) : A->rec + (size_t)chunk0 * kChunkRecBytes;
   // position p of token t: piece p ^ (t mod 8)
+  const int piece = (lane & 7) ^ (lane >> 3);
+  const uint32_t row_off = (uint32_t)min(8 * wave + (lane >> 3), batch - 1) * (uint32_t)cols * 2u + 16u * (uint32_t)piece;
   uint32_t extra_off =
-      x_wave ? (uint32_t)min(8 * wave + (lane >> 3), batch - 1) * (uint32_t)cols * 2u + 16u * (uint32_t)((lane & 7) ^ (lane >> 3))
+      x_wave ? row_off
              : (uint32_t)min(1024 * min(max(wave - (NP > 0 ? NT / 8 : 0), 0), 2) + 16 * lane, kChunkRecBytes - 16);
   const int pieces = NP > 0 ? NP : (int)((slot + kPieceBytes - 1) / kPieceBytes);
   // values [t0, t1) of a chunk into the slot at `to`
@@ -142,16 +151,16 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
     uint32_t to = x0 + C::kWarm, off = extra_off;
     if (x_wave) {
       to = x0 + (uint32_t)((s & (kXAhead - 1)) * C::kXBytes + 1024 * wave);
-      off -= 16u * (uint32_t)pieces_back(c0 + s, (lane & 7) ^ (lane >> 3), cols);
+      off -= 16u * (uint32_t)pieces_back(c0 + s, piece, cols);
     }
     dma16(extra, off, (uint32_t)__builtin_amdgcn_readfirstlane((int)to));
     extra_off += x_wave ? 2u * kChunkCols : (uint32_t)kChunkRecBytes;
   };
-  // unaligned rows: the activations of chunk s by elements
-  auto copy_x = [&](int s) __attribute__((always_inline)) {
+  // unaligned rows: the activations of chunk c by elements, to raw slot s
+  auto copy_x = [&](int s, int c) __attribute__((always_inline)) {
     if (threadIdx.x >= NT * 8) return;
     const int t = min((int)(threadIdx.x >> 3), batch - 1);
-    const int k = (c0 + s) * kChunkCols + 8 * ((lane & 7) ^ (lane >> 3));
+    const int k = c * kChunkCols + 8 * piece;
     const uint16_t* const x = A->x + (size_t)t * cols;
     uint32_t h[8];
 #pragma unroll
@@ -228,6 +237,46 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
     prec += step;
   };
 
+  if constexpr (!BMASK) {
+    // A gated product: every workgroup counts the columns of the sample that
+    // are active for some token (wave w: chunk w mod 4, half the tokens) and
+    // leaves if they are too few; all of the product's see the same sample.
+    uint32_t* const gate = A->gate;
+    if (gate) {
+#pragma unroll
+      for (int j = 0; j < kSampleChunks; ++j) {
+        const int c = sample_chunk(j, A->chunks);
+        if (NP == 0)
+          copy_x(j, c);
+        else if (x_wave)
+          dma16(A->x, row_off + (uint32_t)(c * kChunkCols * 2) - 16u * (uint32_t)pieces_back(c, piece, cols),
+                (uint32_t)__builtin_amdgcn_readfirstlane((int)(x0 + (uint32_t)(j * C::kXBytes + 1024 * wave))));
+      }
+      wait_barrier<0>();
+      const int c = sample_chunk(word, A->chunks);
+      const uint32_t raw = x0 + (uint32_t)(word * C::kXBytes) + 2u * (uint32_t)(lane & 7);
+      const uint32_t lo = (uint32_t)(A->code + 1);
+      bool on = false;
+#pragma unroll
+      for (int i = 0; i < NT / 2; ++i) {  // rows past the batch repeat its last token
+        const int t = half * (NT / 2) + i;
+        const uint32_t h = *at<uint16_t>(raw + 128u * t + 16u * (uint32_t)((lane >> 3) ^ (t & 7))) & 0x7FFFu;
+        on = on || (h >= lo && h <= 0x7C00u);
+      }
+      const uint64_t act = __builtin_amdgcn_ballot_w64(on && c * kChunkCols + lane < cols);
+      if (lane == 0) *at<uint64_t>(x0 + C::kMasked + 8u * (uint32_t)wave) = act;
+      wait_barrier<0>();
+      int active = 0;
+#pragma unroll
+      for (int j = 0; j < kSampleChunks; ++j)
+        active += __builtin_popcountll(*at<uint64_t>(x0 + C::kMasked + 8u * j) |
+                                       *at<uint64_t>(x0 + C::kMasked + 8u * (j + 4)));
+      const bool all = __builtin_amdgcn_readfirstlane(active) >= A->gate_min;
+      if (local == 0 && threadIdx.x == 0) *gate = all ? 1u : 0u;
+      if (!all) return;
+    }
+  }
+
   // prologue: a chunk of values, four of activations
   uint32_t t0 = co[0], t1 = co[1];
   issue_values(t0, t1, l0);
@@ -236,7 +285,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
 #pragma unroll
   for (int s = 0; s < kXAhead; ++s)
     if (s < n) {
-      if (NP == 0) copy_x(s);
+      if (NP == 0) copy_x(s, c0 + s);
       issue_extra(s);
     }
   fetch(4 * kRecBytes);
@@ -263,7 +312,7 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
     // the next chunk replaces the one whose readers the barrier has seen out
     if (s + 1 < n) issue_values(t0, t1, l0 + (uint32_t)((s + 1) & 1) * slot);
     if (s + kXAhead < n) {
-      if (NP == 0) copy_x(s + kXAhead);
+      if (NP == 0) copy_x(s + kXAhead, c0 + s + kXAhead);
       issue_extra(s + kXAhead);
     }
 
@@ -327,9 +376,9 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
       sum[e] = half == 0 ? acc[0][e] + other[e * 64 + lane] : other[e * 64 + lane] + acc[1][e];
   }
 
-  const_ptr<LaunchArgs> kl = (const_ptr<LaunchArgs>)__builtin_amdgcn_kernarg_segment_ptr();
+  const_ptr<WideLaunch> kl = (const_ptr<WideLaunch>)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(kl));
-  const const_ptr<MatArgs> ka = &kl->m[blockIdx.y];
+  const const_ptr<WideArgs> ka = &kl->m[blockIdx.y];
   const int nb = kl->batch;
   const int n_seg = ka->segments;
   const int rows = ka->rows;
@@ -488,7 +537,7 @@ __global__ __launch_bounds__(256) void flag_nonfinite_kernel(const uint4* v, lon
 }
 
 template <int NT, bool BMASK, int NP>
-hipError_t launch(const LaunchArgs& args, dim3 grid, hipStream_t stream) {
+hipError_t launch(const WideLaunch& args, dim3 grid, hipStream_t stream) {
   const int lds = WideCfg<NT>::lds(args.slot);
   const auto kernel = wide_kernel<NT, BMASK, NP>;
   if (lds > 64 * 1024) {
@@ -501,7 +550,7 @@ hipError_t launch(const LaunchArgs& args, dim3 grid, hipStream_t stream) {
 }
 
 template <int NT, bool BMASK>
-hipError_t launch_loads(const LaunchArgs& args, bool aligned, dim3 grid, hipStream_t stream) {
+hipError_t launch_loads(const WideLaunch& args, bool aligned, dim3 grid, hipStream_t stream) {
   if (!aligned) return launch<NT, BMASK, 0>(args, grid, stream);
   switch ((args.slot + kPieceBytes - 1) / kPieceBytes) {
     case 1: return launch<NT, BMASK, 1>(args, grid, stream);
@@ -513,7 +562,7 @@ hipError_t launch_loads(const LaunchArgs& args, bool aligned, dim3 grid, hipStre
 
 }  // namespace
 
-hipError_t launch_wide(const LaunchArgs& args, int count, bool bmask, dim3 grid, hipStream_t stream) {
+hipError_t launch_wide(const WideLaunch& args, int count, bool bmask, dim3 grid, hipStream_t stream) {
   bool aligned = true;
   for (int i = 0; i < count; ++i) aligned = aligned && args.m[i].cols % 8 == 0;
   if (args.batch <= 8)
@@ -554,7 +603,7 @@ int lay_out_records(spdp_matrix* m) {
   for (size_t i = 0; i + 1 < off.size(); ++i) widest = std::max(widest, off[i + 1] - off[i]);
   // and slack for the records that the loops request past the end
   const size_t bytes = (size_t)(m->n_stripes * chunks + 3) * kChunkRecBytes;
-  // the offsets, then the flag of the values' check
+  // the offsets, then the flag of the values' check, which later is the gate
   const size_t off_bytes = off.size() * sizeof(uint32_t);
   hipError_t e = hipMalloc(&m->d_chunk_off, off_bytes + 256);
   if (e == hipSuccess) e = hipMalloc(&m->d_rec, bytes);
@@ -588,6 +637,7 @@ int lay_out_records(spdp_matrix* m) {
   e = hipMemcpy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost);  // waits for both kernels
   if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
   m->finite = bad == 0;
+  m->d_gate = flag;
   m->chunks = (int)chunks;
   m->chunk_bytes = std::max(1024, (int)((widest + 1023) / 1024 * 1024));
   return SPDP_OK;

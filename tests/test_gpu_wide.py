@@ -146,3 +146,125 @@ def test_noalloc_gives_the_same_bits_and_follows_smaller_calls():
             assert np.array_equal(got, _run(m, x, 0.6, "token"))
     for m in ms:
         m.close()
+
+
+def _cancelling(rows, cols, batch, active, seed):
+    """Weights and tokens whose exact products are 0 (column j + cols / 2
+    takes back column j), so that the outputs are nothing but the rounding of
+    the summation order: they tell which form ran. Column j is active (for one
+    of the tokens) where ``active`` holds for j mod (cols / 2)."""
+    rng = np.random.default_rng(seed)
+    half = cols // 2
+    w = (rng.standard_normal((rows, half)) * (rng.random((rows, half)) < 0.6)).astype(np.float16)
+    x = (100.0 * rng.standard_normal((batch, half))).astype(np.float16)
+    x[np.abs(x) < 1.0] = 1.5
+    one = rng.integers(0, batch, half)
+    low = np.arange(batch)[:, None] != one[None, :]  # inactive but for one token a column
+    low |= ~active[:half][None, :]
+    x[low] = 0.5
+    w = np.concatenate([w, -w, np.zeros((rows, cols - 2 * half), np.float16)], 1)
+    x = np.concatenate([x, x, np.zeros((batch, cols - 2 * half), np.float16)], 1)
+    return w, x
+
+
+def _sample(cols):
+    """The sampled columns: the middle chunks of the width's quarters."""
+    chunks = -(-cols // 64)
+    firsts = [64 * ((2 * j + 1) * chunks // 8) for j in range(4)]
+    return np.concatenate([np.arange(f, min(f + 64, cols)) for f in firsts])
+
+
+@pytest.mark.parametrize("rows,cols,tile_k,batch", [
+    (300, 4096, 16, 5), (300, 4096, 16, 8), (700, 3000, 32, 9), (257, 2056, 128, 16),
+    (300, 4095, 16, 8), (300, 1001, 16, 17), (520, 6400, 16, 32),
+])
+@pytest.mark.parametrize("call", ["spmspv", "noalloc", "many"])
+def test_gated_calls_pick_their_form_from_the_activations(rows, cols, tile_k, batch, call, monkeypatch):
+    # all columns active, none, and one column of the sample more and less
+    # than the share that the rule asks for (0.7, 0.5, 0.3 by batch)
+    share = 0.7 if batch <= 8 else 0.5 if batch <= 16 else 0.3
+    sample = _sample(cols)
+    need = int(np.ceil(np.float32(share) * np.float32(len(sample))))
+    half = cols // 2
+    in_sample = np.zeros(half, int)  # how many sampled columns column j mod half stands for
+    for k in sample:
+        if k < 2 * half:
+            in_sample[k % half] += 1
+    rng = np.random.default_rng(batch)
+    order = rng.permutation(np.nonzero(in_sample)[0])
+    taken = np.cumsum(in_sample[order])
+    cases = {"all": (np.ones(half, bool), True), "none": (np.zeros(half, bool), False)}
+    for name, n in (("above", int(np.searchsorted(taken, need)) + 1), ("below", int(np.searchsorted(taken, need)))):
+        on = np.zeros(half, bool)
+        on[order[:n]] = True
+        others = in_sample == 0
+        on[others] = rng.random(int(others.sum())) < 0.5  # not looked at
+        cases[name] = (on, name == "above")
+    if need > taken[-1]:
+        cases.pop("above")
+    for name, (on, expect_all) in cases.items():
+        w, x = _cancelling(rows, cols, batch, on, 7 + batch)
+        m = spdp.encode(w, (256, tile_k))
+        other = spdp.encode(w[: min(rows, 64)], (256, tile_k)) if call == "many" else None
+        X = _to_dev(x)
+        Y = torch.empty((batch, rows), dtype=torch.float16, device=X.device)
+        Z = torch.empty((batch, min(rows, 64)), dtype=torch.float16, device=X.device)
+
+        def product(wide):
+            monkeypatch.setenv("SPDP_WIDE", wide)
+            out = []
+            for _ in range(2):
+                Y.fill_(float("nan"))
+                if call == "noalloc":
+                    m.spmspv_noalloc_into(X, 1.0, Y)
+                elif call == "many":
+                    spdp.spmspv_many([other, m], [X, X], [1.0, 1.0], [Z, Y])
+                else:
+                    m.spmspv_into(X, 1.0, Y)
+                out.append(Y.cpu().numpy().view(np.uint16))
+            assert np.array_equal(out[0], out[1])
+            return out[0]
+
+        gated, columns, every = product("-5"), product("0"), product("5")
+        if name != "none":
+            assert not np.array_equal(columns, every), name  # the inputs tell the forms apart
+        assert np.array_equal(gated, every if expect_all else columns), name
+        # per-column sums of 100-sized terms: rounding only
+        assert np.abs(gated.view(np.float16).astype(np.float64)).max() < 1.0, name
+        m.close()
+        if other is not None:
+            other.close()
+
+
+def test_a_captured_gated_call_follows_its_inputs(monkeypatch):
+    # the gate is set and read inside the call: replays choose anew
+    monkeypatch.setenv("SPDP_WIDE", "-5")
+    rows, cols, batch = 512, 4096, 12
+    inputs = []
+    for seed, u in ((1, 1.0), (2, 0.05), (3, 1.0), (4, 0.0), (5, 0.3)):
+        on = np.random.default_rng(seed).random(cols // 2) < u
+        inputs.append(_cancelling(rows, cols, batch, on, 5)[1])
+    w, _ = _cancelling(rows, cols, batch, np.ones(cols // 2, bool), 5)
+    m = spdp.encode(w, (256, 16))
+    m.reserve(batch)
+    X = torch.empty((batch, cols), dtype=torch.float16, device="cuda:0")
+    Y = torch.empty((batch, rows), dtype=torch.float16, device="cuda:0")
+    want = []
+    for x in inputs:
+        X.copy_(_to_dev(x))
+        m.spmspv_into(X, 1.0, Y)
+        want.append(Y.clone())
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        m.spmspv_into(X, 1.0, Y)
+    for _ in range(3):
+        for x, y in zip(inputs, want):
+            X.copy_(_to_dev(x))
+            Y.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(Y.view(torch.int16), y.view(torch.int16))
+    del g
+    m.close()

@@ -51,6 +51,11 @@ int main() {
         if (from < 0 || from + 8 > cols || (k < cols && from != k)) return std::printf("%d %d %d\\n", cols, c, p), 1;
         seen += k < cols;
       }
+    for (int j = 0; j < kSampleChunks; ++j) {
+      const int c = sample_chunk(j, (int)chunk_count(cols));
+      if (c < 0 || c >= chunk_count(cols)) return std::printf("%d: sample %d\\n", cols, j), 1;
+    }
+    if (sample_columns((int)chunk_count(cols), cols) < 1) return 1;
     if (seen != cols / 8) return std::printf("%d: %d pieces\\n", cols, seen), 1;
   }
   return std::printf("%ld\\n", n) < 0;
@@ -210,3 +215,17 @@ def test_encode_without_host_memory_for_the_records(fake_hip):
     out["live"] = hip.fake_live()
     """)
     assert out == {"0": True, "388": False, "live": 0}, out
+
+
+def test_a_call_that_cannot_be_launched_launches_nothing(fake_hip):
+    # a gated product is two launches: what can fail is asked before the first
+    out = run(fake_hip, """
+    m = ones(300, 6400, (256, 16), 1.0)  # dense: more than 64 KB of LDS
+    hip.fake_fail_attribute(1)
+    log()
+    out["status"] = many([m], 8)
+    out["launches"] = len(launches())
+    hip.fake_fail_attribute(0)
+    out["after"] = many([m], 8)
+    """)
+    assert out == {"status": -4, "launches": 0, "after": 0}, out
