@@ -155,7 +155,9 @@ int spdp_spmspv_noalloc(spdp_handle_t h, const uint16_t* X, int32_t batch,
                         float threshold, uint16_t* Y, void* stream);
 
 /*
- * spdp_spmspv_many -- several independent products in one launch:
+ * spdp_spmspv_many -- several independent products in one launch (two where
+ * spdp_spmspv samples X; products of one width take the same route up to
+ * that width's size limits):
  * Y[i] = W_i . mask(X[i]) with threshold thresholds[i], for i < count. This
  * is how a decoder issues the projections that read the same layer input
  * (q, k and v; gate and up), whose fixed per-launch latency would otherwise
@@ -174,7 +176,7 @@ int spdp_spmspv_noalloc(spdp_handle_t h, const uint16_t* X, int32_t batch,
  *   stream      hipStream_t to enqueue on.
  *
  * Errors are those of spdp_spmspv plus SPDP_ERR_INVALID_ARG for a bad count,
- * a repeated handle, mixed tile_m or overlapping outputs; on any error
+ * a repeated handle, mixed tile_m or overlapping outputs; on any of these
  * nothing is launched. spdp_spmspv(h, ...) is this call with count 1.
  */
 int spdp_spmspv_many(const spdp_handle_t* handles, int32_t count,

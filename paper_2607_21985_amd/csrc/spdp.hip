@@ -1345,12 +1345,16 @@ int early_first(int batch, int64_t workgroups) {
 //     that such masks leave, and so do three grouped above 16 tokens, where
 //     every workgroup sums all tokens' scores (1792x1600 at 25 % and 25
 //     tokens 20.7 - 22.9).
-// A property of the matrix, the batch,
+// Products that read one input (q, k and v) should take one route, or their
+// call is two launches in a row (with an ungated k and v, 8192x8192 and twice
+// 1024x8192 at 8 tokens and u = 0.7 30.8 - 41.9): so no width beyond 5120
+// counts as small up to 16 tokens, q being large there. A property of the matrix, the batch,
 // the mask and the activations, so a product gives the same bits alone and
 // grouped. SPDP_WIDE overrides the token count from which the form runs (0:
 // never; -n: gated from n tokens, at least 5; for tuning).
 enum Route { kPerColumn, kAllColumns, kGated };
 constexpr int64_t kWideMedium = 100000000;  // weights, the zeros included
+constexpr int64_t kWideSmallCols = 5120;
 Route choose_route(const spdp_matrix* h, int batch, bool bmask, int32_t code) {
   if (!h->d_rec || !h->finite || batch < 2 || use_mfma(batch)) return kPerColumn;
   if (const char* env = std::getenv("SPDP_WIDE")) {
@@ -1359,7 +1363,7 @@ Route choose_route(const spdp_matrix* h, int batch, bool bmask, int32_t code) {
     return from > 0 && batch >= from ? kAllColumns : kPerColumn;
   }
   const int64_t weights = h->rows * h->cols;
-  const bool small = weights <= (batch < 8 || bmask ? 20000000 : 27000000);
+  const bool small = weights <= (batch < 8 || bmask ? 20000000 : 27000000) && h->cols <= kWideSmallCols;
   if (bmask) return small && batch >= 8 && batch <= 16 ? kAllColumns : kPerColumn;
   if (batch < 5) return kPerColumn;
   if (small) return batch <= 8 && h->rows > 8 * h->cols ? kPerColumn : kAllColumns;

@@ -217,6 +217,41 @@ def test_encode_without_host_memory_for_the_records(fake_hip):
     assert out == {"0": True, "388": False, "live": 0}, out
 
 
+def test_launches_of_a_grouped_call(fake_hip):
+    # q, k and v of the 70B layer: one launch where no product is gated (4
+    # tokens, one mask for the batch), and never more than two, the second
+    # only with products that the first is a gate for; every column kept
+    # (a negative threshold): one
+    out = run(fake_hip, """
+    q = ones(8192, 8192, (256, 16), 0.02)
+    k = ones(1024, 8192, (256, 16), 0.02, 1)
+    v = ones(1024, 8192, (256, 16), 0.02, 2)
+    for tokens in (1, 2, 4, 5, 8, 16, 32):
+        for mask in (0, 1):
+            for t in (0.5, -1.0):
+                log()
+                assert many([q, k, v], tokens, mask, [t] * 3) == 0
+                out[f"{tokens} {mask} {t}"] = [("wide" if "wide" in n else "columns", g[1]) for n, g in launches()]
+    s = ones(2048, 2048, (256, 16), 0.02)
+    for tokens in (4, 5, 8, 32):
+        log()
+        assert many([s], tokens) == 0
+        out[f"small {tokens}"] = [("wide" if "wide" in n else "columns", g[1]) for n, g in launches()]
+    """)
+    for key, got in out.items():
+        if key.startswith("small"):
+            want = [["columns" if key == "small 4" else "wide", 1]]
+        else:
+            tokens, mask, t = key.split()
+            if int(tokens) < 5 or mask == "1":
+                want = [["columns", 3]]
+            elif t == "-1.0" or int(tokens) > 16:
+                want = [["wide", 3]]
+            else:
+                want = [["wide", 3], ["columns", 3]]
+        assert got == want, (key, got)
+
+
 def test_a_call_that_cannot_be_launched_launches_nothing(fake_hip):
     # a gated product is two launches: what can fail is asked before the first
     out = run(fake_hip, """
