@@ -703,10 +703,11 @@ struct RowArgs {
   int slot;           // LDS bytes of a chunk's values (a multiple of 1024)
 };
 
-// The sums of the chunks [c0, c0 + n) of a stripe. XV: X rows are 16-byte
-// aligned (else they are read by elements).
-template <int TB, bool XV>
-__device__ __forceinline__ void rows_range(const RowArgs& a, unsigned char* lds, int c0, int n, float (&sum)[TB][16]) {
+// The sums of the chunks [c0, c0 + n) of a stripe, element e of token block j
+// to emit(j, e, sum) (rows below a.rows only, unless ALL). XV: X rows are
+// 16-byte aligned (else they are read by elements).
+template <int TB, bool XV, bool ALL, class Emit>
+__device__ __forceinline__ void rows_range(const RowArgs& a, unsigned char* lds, int c0, int n, Emit emit) {
   using namespace spdp_dev;
   using C = RowCfg<TB>;
   const int lane = threadIdx.x & 63;
@@ -825,12 +826,13 @@ __device__ __forceinline__ void rows_range(const RowArgs& a, unsigned char* lds,
     for (int e = 0; e < 16; ++e)
       red[((wave * TB + j) * 16 + e) * 64 + lane] = half == 0 ? acc[1][j][e] : acc[0][j][e];
   __syncthreads();
+  if (!ALL && r * kTM + 64 * word + 32 * half + (lane & 31) >= a.rows) return;
 #pragma unroll
   for (int j = 0; j < TB; ++j)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const float other = red[(((wave ^ 4) * TB + j) * 16 + e) * 64 + lane];
-      sum[j][e] = half == 0 ? acc[0][j][e] + other : other + acc[1][j][e];
+      emit(j, e, half == 0 ? acc[0][j][e] + other : other + acc[1][j][e]);
     }
 }
 
@@ -847,39 +849,37 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((FOLD ? 4 :
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long nb0 = (long long)blockIdx.y * RowCfg<TB>::kTokens;
   const int last_tok = (int)min(a.n_tokens - nb0, (long long)RowCfg<TB>::kTokens) - 1;
-  float sum[TB][16];
+  const int row = (int)blockIdx.x * kTM + 64 * (wave & 3) + 32 * (wave >> 2) + (lane & 31);
+  const bool split = gridDim.z > 1;
+  float* const part = a.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows;
+  auto store = [&](int j, int e, float sum) __attribute__((always_inline)) {
+    const int t = 32 * j + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    if (t > last_tok) return;
+    const size_t at = (size_t)(nb0 + t) * (size_t)a.rows + (size_t)row;
+    if (split)
+      part[at] = sum;
+    else
+      a.y[at] = __half_as_ushort(__float2half_rn(sum));
+  };
   if constexpr (FOLD) {
-    rows_range<TB, XV>(a, lds, 0, min(a.cps, a.chunks), sum);
+    float total[TB][16];
+    rows_range<TB, XV, true>(a, lds, 0, min(a.cps, a.chunks), [&](int j, int e, float sum) __attribute__((always_inline)) {
+      total[j][e] = sum;
+    });
     for (int c0 = a.cps; c0 < a.chunks; c0 += a.cps) {
       __syncthreads();  // the range before has been read out of the LDS
-      float next[TB][16];
-      rows_range<TB, XV>(a, lds, c0, min(a.cps, a.chunks - c0), next);
+      rows_range<TB, XV, true>(a, lds, c0, min(a.cps, a.chunks - c0),
+                               [&](int j, int e, float sum) __attribute__((always_inline)) { total[j][e] += sum; });
+    }
+    if (row < a.rows)
 #pragma unroll
       for (int j = 0; j < TB; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) sum[j][e] += next[j][e];
-    }
+        for (int e = 0; e < 16; ++e) store(j, e, total[j][e]);
   } else {
     const int c0 = (int)blockIdx.z * a.cps;
-    rows_range<TB, XV>(a, lds, c0, min(a.cps, a.chunks - c0), sum);  // at least one chunk
+    rows_range<TB, XV, false>(a, lds, c0, min(a.cps, a.chunks - c0), store);  // at least one chunk
   }
-
-  const int row = (int)blockIdx.x * kTM + 64 * (wave & 3) + 32 * (wave >> 2) + (lane & 31);
-  if (row >= a.rows) return;
-  const bool split = gridDim.z > 1;
-  float* const part = a.part + (size_t)blockIdx.z * (size_t)a.n_tokens * (size_t)a.rows;
-#pragma unroll
-  for (int j = 0; j < TB; ++j)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int t = 32 * j + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-      if (t > last_tok) continue;
-      const size_t at = (size_t)(nb0 + t) * (size_t)a.rows + (size_t)row;
-      if (split)
-        part[at] = sum[j][e];
-      else
-        a.y[at] = __half_as_ushort(__float2half_rn(sum[j][e]));
-    }
 }
 
 // Y = fp16(sum over the splits of part[z]), the splits added in order
