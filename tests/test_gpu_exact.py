@@ -134,7 +134,7 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("label,rows,cols,tile,points,batches,seed", SHAPES, ids=[s[0] for s in SHAPES])
-def test_exact_every_row(label, rows, cols, tile, points, batches, seed):
+def test_exact_every_row(monkeypatch, label, rows, cols, tile, points, batches, seed):
     for sw, p in points:
         w = _pruned(rows, cols, seed, sw)
         m = spdp.encode(w, tile)
@@ -143,8 +143,14 @@ def test_exact_every_row(label, rows, cols, tile, points, batches, seed):
             t = float(oracle.threshold_for(x, p))
             lab = f"{label} sw={sw} p={p} B={b} token mask"
             print(f"[gpu-exact] {lab}", flush=True)
-            _assert_bits(_run(m, x, t, "token"), _expected_bits(w, x, t, "token"), lab)
+            expect = _expected_bits(w, x, t, "token")
+            _assert_bits(_run(m, x, t, "token"), expect, lab)
             if b > 1:
+                # the rule may take the all-columns form: the per-column
+                # kernels too
+                monkeypatch.setenv("SPDP_WIDE", "0")
+                _assert_bits(_run(m, x, t, "token"), expect, lab + " per column")
+                monkeypatch.delenv("SPDP_WIDE")
                 tb = _batch_t(x, p)
                 lab = f"{label} sw={sw} p={p} B={b} batch mask"
                 print(f"[gpu-exact] {lab}", flush=True)
@@ -159,6 +165,7 @@ def test_exact_every_row(label, rows, cols, tile, points, batches, seed):
 @pytest.mark.parametrize("rows,cols,batch,seed", [(28672, 8192, 32, 20), (1000, 3000, 17, 51)],
                          ids=["28672x8192 B=32", "1000x3000 B=17"])
 def test_exact_one_segment(monkeypatch, rows, cols, batch, seed, mfma):
+    monkeypatch.setenv("SPDP_WIDE", "0")
     monkeypatch.setenv("SPDP_PASSES", "64")
     monkeypatch.setenv("SPDP_MFMA", mfma)
     w = _pruned(rows, cols, seed, 0.7)

@@ -234,7 +234,12 @@ def _edge_x(batch, cols):
     (32, "token", None, False), (2, "batch", None, False), (8, "batch", None, False),
     (20, "batch", None, False), (32, "batch", None, False),
     (1, "token", None, True), (4, "token", None, True), (16, "token", None, True), (32, "token", None, True)])
-def test_threshold_edges_every_form(monkeypatch, batch, mask, mfma, codes):
+@pytest.mark.parametrize("wide", ["0", None], ids=["columns", "rule"])
+def test_threshold_edges_every_form(monkeypatch, batch, mask, mfma, codes, wide):
+    # the per-column kernels, and whatever the rule takes (from 5 tokens the
+    # all-columns form)
+    if wide is not None:
+        monkeypatch.setenv("SPDP_WIDE", wide)
     if mfma is not None:
         monkeypatch.setenv("SPDP_MFMA", mfma)
     w = oracle.magnitude_prune(synth.weights(300, 512, 23), 0.5)
@@ -251,7 +256,7 @@ def test_threshold_edges_every_form(monkeypatch, batch, mask, mfma, codes):
     else:
         m = spdp.encode(w, (256, 16))
     for t in _EDGE_THRESHOLDS:
-        label = f"B={batch} mask={mask} mfma={mfma} codes={codes} t={t}"
+        label = f"B={batch} mask={mask} mfma={mfma} codes={codes} wide={wide} t={t}"
         print(f"[gpu] edges {label}", flush=True)
         y = _run_gpu(m, x, t, mask=mask)
         y64, s64, _ = oracle.spmspv_rtn(q, scales, x, t, mask) if codes else oracle.spmspv(w, x, t, mask)
@@ -570,6 +575,7 @@ def test_forced_passes_and_matrix_core_form(monkeypatch, passes, batch, mfma):
     without partials."""
     if mfma == "1" and batch < 5:
         pytest.skip("the 32x32 matrix-core form starts at 5 tokens")
+    monkeypatch.setenv("SPDP_WIDE", "0")  # the per-column kernels walk the ranges
     monkeypatch.setenv("SPDP_PASSES", passes)
     monkeypatch.setenv("SPDP_MFMA", mfma)
     w, x, t = _case(700, 3000, (256, 16), 0.6, 0.4, batch, 123, 456)
@@ -584,10 +590,11 @@ def test_forced_passes_and_matrix_core_form(monkeypatch, passes, batch, mfma):
 
 @pytest.mark.parametrize("codes", [False, True], ids=["fp16", "codes"])
 @pytest.mark.parametrize("batch", [1, 2, 3, 8, 16, 32])
-def test_one_segment_every_vector_form(batch, codes):
+def test_one_segment_every_vector_form(monkeypatch, batch, codes):
     """40 columns fit one segment (64 columns at the narrowest split), so
     every stripe's workgroup writes Y itself, also in the one- and two-token
     forms and the code forms (row scale applied at the write)."""
+    monkeypatch.setenv("SPDP_WIDE", "0")
     w, x, t = _case(600, 40, (256, 16), 0.5, 0.3, batch, 131, 457)
     label = f"600x40 B={batch} {'codes' if codes else 'fp16'} one segment"
     print(f"[gpu] {label}", flush=True)

@@ -107,8 +107,8 @@ def test_a_call_covers_the_captures_of_fewer_tokens():
 @pytest.mark.parametrize("rows,cols,tile_k,n", [(512, 4093, 16, 33), (300, 2048, 32, 7), (40960, 264, 16, 128)])
 def test_a_first_call_inside_a_capture(rows, cols, tile_k, n):
     # products that no split warp-specialized form serves (odd widths, other
-    # tile widths, more stripes than half the CUs) run unsplit where the
-    # stream is capturing and there is no workspace to split into
+    # tile widths, more stripes than half the CUs) fold their ranges in the
+    # kernel where the stream is capturing and there is no workspace
     w, x = _inputs(rows, cols, n, 0.5, 9)
     m = spdp.encode(w, (256, tile_k))
     X = _to_dev(x)

@@ -1,5 +1,6 @@
 """The all-columns decode form (batches of several tokens): every edge of its
-chunks (64 columns), groups (16) and tiles against the oracle, bit for bit on
+chunks (64 columns), groups (16) and tiles against the oracle and the
+per-column kernels, bit for bit on
 inputs whose fp32 sums are exact in any order (weights k 2^-9 with |k| < 16,
 activations j / 4 with |j| <= 8: every partial sum is a multiple of 2^-11 below
 2^11 at these widths, so it has at most 22 bits)."""
@@ -77,7 +78,10 @@ def test_every_row_exact(monkeypatch, rows, cols, tk, sw, batch, splits, mask):
         t = t * (0.8 if mask == "batch" else 1.0)
         print(f"[gpu-wide] {rows}x{cols} tile_k={tk} sw={sw} B={batch} {mask} t={t} splits={splits}", flush=True)
         xt = x if t >= 0 else np.nan_to_num(x)
-        assert np.array_equal(_run(m, xt, t, mask), _expected(w, xt, t, mask))
+        expect = _expected(w, xt, t, mask)
+        for form in ("2", "0"):  # all columns, and the per-column kernels
+            monkeypatch.setenv("SPDP_WIDE", form)
+            assert np.array_equal(_run(m, xt, t, mask), expect), form
     m.close()
 
 
