@@ -25,6 +25,7 @@ struct spdp_matrix {
   std::vector<float> scales;
 
   int device = -1;  // -1: host-only handle
+  int cus = 0;      // the device's compute units
   void* d_tile_offset = nullptr;
   void* d_col_info = nullptr;
   void* d_bitmap = nullptr;

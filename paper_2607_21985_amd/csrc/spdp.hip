@@ -1385,7 +1385,7 @@ float gate_share(const spdp_matrix* h, int batch) {
 // Chunks (64 columns) per segment of the all-columns form: at most `segments`
 // segments (the per-column plan's, so that the partials fit the same
 // workspace), the count that a model of the launch puts at the least time.
-// With m workgroups per CU (of 256), three of them resident, a chunk takes
+// With m workgroups per CU, three of them resident, a chunk takes
 // 1.6, 1.75 or 2 us (one, two, three resident: from three on the vector ALUs
 // are the limit, 200 instructions per chunk and wave) and a workgroup 3 us
 // and 0.2 us per token (prologue; partials, 8 bytes per row and token).
@@ -1399,7 +1399,7 @@ int wide_seg_chunks(const spdp_matrix* h, int batch, int segments) {
   for (int s = 1; s <= std::min(segments, h->chunks); ++s) {
     const int per = (h->chunks + s - 1) / s;
     if ((h->chunks + per - 1) / per != s) continue;
-    const int64_t m = (stripes * s + 255) / 256;
+    const int64_t m = (stripes * s + h->cus - 1) / h->cus;
     constexpr float kLast[3] = {0.0f, 1.6f, 1.75f};
     const float us = (float)per * (2.0f * (float)(m / 3) + kLast[m % 3]) + (float)m * (3.0f + 0.2f * (float)batch);
     if (s == 1 || us < least) {
@@ -1542,7 +1542,9 @@ int finish_device(spdp_matrix* m, spdp_handle_t* out) {
     return hip_fail(e, "hipGetDevice");
   }
   m->device = dev;
-  int st = upload(m->tile_offset, &m->d_tile_offset);
+  e = hipDeviceGetAttribute(&m->cus, hipDeviceAttributeMultiprocessorCount, dev);
+  int st = e == hipSuccess ? SPDP_OK : hip_fail(e, "hipDeviceGetAttribute");
+  if (st == SPDP_OK) st = upload(m->tile_offset, &m->d_tile_offset);
   if (st == SPDP_OK) st = upload(m->col_info, &m->d_col_info);
   if (st == SPDP_OK) st = upload(m->bitmap, &m->d_bitmap);
   if (st == SPDP_OK) st = m->value_bits < 16 ? upload(m->codes, &m->d_values) : upload(m->values, &m->d_values);

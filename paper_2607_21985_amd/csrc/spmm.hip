@@ -37,8 +37,7 @@
 
 namespace {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
+using namespace spdp_dev;
 
 constexpr int kTM = 256;                       // rows of a stripe (four bitmap words per column)
 constexpr int kKStep = 16;                     // columns per k-step (the MFMA's k)
@@ -68,9 +67,6 @@ struct SpmmArgs {
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
-
-template <class T>
-using const_ptr = const __attribute__((address_space(4))) T*;
 
 // The plain form. What one wave fetches for one k-step: its four columns'
 // values (one per lane and bitmap word, 0 where the bit is clear) and its B
@@ -191,17 +187,8 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs a) {
 constexpr int kValBytes = kTM * kKStep * 2;    // a dense GTile's worth of values
 constexpr int kXBytes = kBN * kKStep * 2;      // 128 tokens x 16 columns
 
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-// Global -> LDS DMA (lane l's bytes land at lds + 16 l, or + 4 l). Issued as
-// assembly so that the compiler does not order LDS reads of other ring
-// slots behind every outstanding load; the waits are explicit. The compiler
-// does not look inside assembly for hazards: a vector memory instruction
-// needs 5 wait states after a VALU write of an SGPR it reads, hence s_nop 4.
-__device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
-}
+// Global -> LDS DMA of 4 bytes per lane (lane l's bytes land at lds + 4 l),
+// as dma16 of expand.h.
 __device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t lds) {
   asm volatile("s_nop 4\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
 }
@@ -243,14 +230,6 @@ constexpr int kWsRing = 8;
 constexpr int kWsDma = 2;      // loads per step of a multiplying wave
 constexpr int kToCap = 1800;   // TileOffsets of one stripe's split held in LDS
 constexpr int kGBytes = kValBytes + kXBytes;  // one GTile's values and X block in a ring slot
-
-// the lane's value where its bit of the word is set, else 0 (the word as
-// the select mask of a VOP3 select: no move through vcc)
-__device__ __forceinline__ uint32_t select_word(uint32_t v, uint64_t mask) {
-  uint32_t r;
-  asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(v), "s"(mask));
-  return r;
-}
 
 // wait until at most kWsDma x `later` loads are in flight (later < N + 1)
 template <int N>
@@ -684,7 +663,7 @@ __global__ __launch_bounds__(kW256Waves * 64) void spmm_ws256_kernel(WsArgs wa) 
 template <int TB>
 struct RowCfg {
   static constexpr int kTokens = 32 * TB;
-  static constexpr int kXBytes = kTokens * spdp_dev::kChunkCols * 2;
+  static constexpr int kXBytes = kTokens * kChunkCols * 2;
   static constexpr int kRedBytes = 8 * TB * 16 * 64 * 4;  // half of every wave's accumulators
   static int lds(int slot) { return std::max(2 * (slot + kXBytes) + 1024, kRedBytes); }
 };
@@ -708,7 +687,6 @@ struct RowArgs {
 // 16-byte aligned (else they are read by elements).
 template <int TB, bool XV, bool ALL, class Emit>
 __device__ __forceinline__ void rows_range(const RowArgs& a, unsigned char* lds, int c0, int n, Emit emit) {
-  using namespace spdp_dev;
   using C = RowCfg<TB>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1195,9 +1173,7 @@ extern "C" int spdp_spmm(spdp_handle_t h, const uint16_t* X, int64_t n_tokens, u
   a.x_vec = h->cols % 8 == 0;
   a.y_vec = h->rows % 4 == 0;
   auto st = static_cast<hipStream_t>(stream);
-  int cus = 0;
-  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+  const int cus = h->cus;
   SpmmPlan plan;
   if (!choose_spmm(h, n_tokens, cus, a.x_vec != 0, &plan))
     return fail(SPDP_ERR_UNSUPPORTED, "the width needs more than 65535 splits");
