@@ -1037,7 +1037,7 @@ def _profile_line(path):
 
 
 def _counters(path):
-    """{counter: ([per spmspv dispatch], [per read-kernel dispatch])}."""
+    """{counter: ([per spMspV kernel dispatch], [per read-kernel dispatch])}."""
     out = {}
     with open(path) as fh:
         for row in csv.DictReader(fh):
@@ -1086,9 +1086,10 @@ def summarize_prefill(d, prof_dir):
     print("\n".join(out))
 
 
-def summarize_sq(d, tag, pj, prof_dir, sha):
+def summarize_sq(d, tag, pj, prof_dir, sha, per_launch):
     """profiles/sq_spmspv_<tag>.txt from three shader-sequencer counter passes:
-    the mean per spMspV dispatch of each counter, the instruction mix per
+    the mean per launch of each counter (a gated launch is two kernel
+    dispatches: ``per_launch`` on average), the instruction mix per
     64-row bitmap word decoded (the algorithmic bitmap bytes / 8), and the
     fractions of the waves' cycles spent issuing and waiting."""
     cs, cmds = {}, []
@@ -1099,13 +1100,14 @@ def summarize_sq(d, tag, pj, prof_dir, sha):
 
     def mean(name):
         v = cs.get(name, ([], []))[0]
-        return sum(v) / len(v) if v else float("nan")
+        return per_launch * sum(v) / len(v) if v else float("nan")
 
     words = pj["line_model_per_launch"]["bitmap"][0] / 8.0
     wc = mean("SQ_WAVE_CYCLES")
     out = [f"# shader-sequencer counters of spmspv_kernel: {tag}", "",
            "commands (GPU box, repository root, TMPDIR=/tmp), one counter pass per run:"] + cmds + [
-           "", f"mean per spMspV dispatch ({len(cs['SQ_WAVES'][0])} dispatches in the first pass):"]
+           "", f"mean per spMspV launch ({len(cs['SQ_WAVES'][0])} kernel dispatches in the first pass, "
+               f"{per_launch:g} per launch):"]
     for p in PASS_S:
         for name in p:
             if name != "GRBM_GUI_ACTIVE" or p is PASS_S[0]:
@@ -1145,9 +1147,11 @@ def summarize_profiles(d, prof_dir=None):
                        f"{float(r['AverageNs']):.1f} | {r['MinNs']} | {r['MaxNs']}")
         kr = [r for r in rows if any(k in r["Name"] for k in ("spmspv_kernel", "spmspv_mm_kernel", "wide_kernel"))]
         calls = sum(int(r["Calls"]) for r in kr)
-        avg = sum(int(r["Calls"]) * float(r["AverageNs"]) for r in kr) / max(calls, 1)
+        # a gated launch is two kernels, of which one leaves at once
+        per_launch = calls / pj["launches"] if calls else 1.0
+        avg = per_launch * sum(int(r["Calls"]) * float(r["AverageNs"]) for r in kr) / max(calls, 1)
         alg = pj["algorithmic_bytes_per_launch"]
-        out += ["", f"all spMspV kernel variants: {calls} launches, launch-weighted average {avg:.1f} ns",
+        out += ["", f"all spMspV kernel variants: {calls} kernels, {per_launch:g} per launch, {avg:.1f} ns per launch",
                 f"  -> {alg / avg:.1f} GB/s algorithmic ({100 * alg / avg / HBM_PEAK_GBS:.2f} % of "
                 f"{HBM_PEAK_GBS:.0f} GB/s)",
                 "", "bench.py --profile-only (same command) reported:",
@@ -1160,7 +1164,7 @@ def summarize_profiles(d, prof_dir=None):
         print("\n".join(out))
 
         if all(os.path.isdir(os.path.join(d, f"pmcS{i + 1}_{tag}")) for i in range(len(PASS_S))):
-            summarize_sq(d, tag, pj, prof_dir, sha)
+            summarize_sq(d, tag, pj, prof_dir, sha, per_launch)
 
         pr, pw = os.path.join(d, f"pmcR_{tag}"), os.path.join(d, f"pmcW_{tag}")
         if not (os.path.isdir(pr) and os.path.isdir(pw)):
@@ -1171,7 +1175,7 @@ def summarize_profiles(d, prof_dir=None):
 
         def mean(c, name, which=0):
             v = c[name][which]
-            return sum(v) / len(v) if v else float("nan")
+            return (per_launch if which == 0 else 1.0) * sum(v) / len(v) if v else float("nan")
 
         n32, n64, n128, nall = (mean(cr, c) for c in PASS_R)
         nw, nw64, nbub, ndram = (mean(cw, c) for c in PASS_W)
@@ -1198,7 +1202,8 @@ def summarize_profiles(d, prof_dir=None):
                f"  bytes by request size = {crd:.0f} = {crd / ref:.4f} x the bytes read",
                f"  FETCH_SIZE's formula (TCC_BUBBLE as the 128-byte count) = {cfetch:.0f} = {cfetch / ref:.4f} x",
                "",
-               f"spmspv_kernel, mean per dispatch ({len(cr[PASS_R[0]][0])} dispatches per pass):",
+               f"spMspV kernels, mean per launch ({len(cr[PASS_R[0]][0])} kernel dispatches per pass, "
+               f"{per_launch:g} per launch):",
                f"  read requests 32/64/128 B = {n32:.0f} / {n64:.0f} / {n128:.0f} (all sizes: {nall:.0f}; "
                f"to DRAM: {ndram:.0f}; TCC_BUBBLE {nbub:.0f})",
                f"  read bytes by request size = {rd:.0f}",

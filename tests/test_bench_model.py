@@ -206,3 +206,39 @@ def test_sq_summary_from_raw_counters(tmp_path):
     assert "issuing 0.450, waiting (any) 0.400, waiting on dependencies 0.150" in sq
     assert "LDS bank conflicts per LDS instruction: 0.0200" in sq
     assert "rocprofv3 --pmc SQ_WAVES" in sq and f"kernel_sha: {bench.kernel_source_sha()}" in sq
+
+
+def test_summaries_count_a_gated_launch_once(tmp_path):
+    """A gated launch is two kernel dispatches: times and counters are summed
+    over both and stated per launch."""
+    d = tmp_path / "raw"
+    out = tmp_path / "profiles"
+    out.mkdir()
+    tag = "wl_decoder"
+    pj = {"profile_only": True, "argv": ["--profile-only", "--workload", "wl"], "ms_per_step": 0.02,
+          "launches": 2, "launches_per_step": 2, "algorithmic_bytes_per_launch": 12000.0,
+          "y_bytes_per_launch": 100.0, "calib_read_bytes": 4096,
+          "line_model_per_launch": {"values": [8000, 8192], "bitmap": [800, 1280], "y": [100, 128]}}
+    for kind in ("trace", "pmcR", "pmcW", "pmcS1", "pmcS2", "pmcS3"):
+        (d / f"{kind}_{tag}").mkdir(parents=True)
+        (d / f"{kind}_{tag}.log").write_text(json.dumps(dict(pj, argv=pj["argv"] + [kind])) + "\n")
+    (d / f"trace_{tag}" / "run_kernel_stats.csv").write_text(
+        '"Name","Calls","TotalDurationNs","AverageNs","Percentage","MinNs","MaxNs","StdDev"\n'
+        '"void wide_kernel<8, false, 2>(WideLaunch)",2,20000,10000.0,90,9000,11000,1\n'
+        '"void spmspv_kernel<8, 4>(LaunchArgs)",2,4000,2000.0,10,1000,3000,1\n')
+    hdr = '"Kernel_Name","Counter_Name","Counter_Value"\n'
+    passes = {"pmcR": bench.PASS_R, "pmcW": bench.PASS_W}
+    passes.update({f"pmcS{i + 1}": p for i, p in enumerate(bench.PASS_S)})
+    for kind, names in passes.items():
+        rows = "".join(f'"{k}","{n}",{v}\n' for n in names
+                       for k, v in (("wide_kernel<8>", 90), ("spmspv_kernel<8, 4>", 10)) * 2)
+        rows += "".join(f'"read_kernel","{n}",32\n' for n in names)
+        (d / f"{kind}_{tag}" / "run_counter_collection.csv").write_text(hdr + rows)
+    bench.summarize_profiles(str(d), str(out))
+    trace = (out / f"spmspv_{tag}_kernel_trace.txt").read_text()
+    assert "kernel_us_per_launch: 12.0000" in trace and "1.0 GB/s algorithmic" in trace
+    traffic = (out / f"traffic_spmspv_{tag}.txt").read_text()
+    assert f"read bytes by request size = {100 * (32 + 64 + 128)}" in traffic
+    assert "= 7168 = 1.7500 x the bytes read" in traffic
+    sq = (out / f"sq_spmspv_{tag}.txt").read_text()
+    assert "instructions per word: VALU 1.00" in sq and "2 per launch" in sq
