@@ -69,7 +69,8 @@ typedef struct spdp_matrix* spdp_handle_t;
  * Device memory for the four arrays plus a small split-K workspace is
  * allocated on the current device and owned by the handle; with tile_m = 256
  * and tile_k >= 16 also 40 bytes per column of every stripe (columns rounded
- * up to 64) for the kernels in which every column takes part (without them,
+ * up to 64; 8 % of the dense fp16 size, 21 % of the four arrays' at 70 %
+ * zeros) for the kernels in which every column takes part (allocated last;
  * where the memory cannot be had, such calls run the other kernels). Returns
  * SPDP_ERR_UNSUPPORTED if the padded values would take 4 GiB or more, or if
  * R * C * tile_k (GTile columns, plus one) reaches 2^26.
@@ -121,10 +122,11 @@ int spdp_encode_host(const uint16_t* W, int64_t rows, int64_t cols,
  * state).
  *
  * Deterministic: the fp32 summation order depends only on the matrix, the
- * batch and which columns are active (and on the tuning variables
- * SPDP_SPLITK, SPDP_PASSES, SPDP_MFMA, SPDP_WIDE and SPDP_EARLY_FIRST, when set), so
- * equal inputs give equal bits on every call, and a product gives the same
- * bits alone and inside spdp_spmspv_many.
+ * batch, the mask and which columns are active; where every column takes
+ * part also on the device's compute-unit count (and on the tuning variables
+ * SPDP_SPLITK, SPDP_PASSES, SPDP_MFMA, SPDP_WIDE and SPDP_EARLY_FIRST, when
+ * set). Equal inputs give equal bits on every call of a handle, and a product
+ * gives the same bits alone and inside spdp_spmspv_many.
  */
 int spdp_spmspv(spdp_handle_t h, const uint16_t* X, int32_t batch,
                 float threshold, uint16_t* Y, void* stream);

@@ -1325,10 +1325,11 @@ int early_first(int batch, int64_t workgroups) {
 //     11008x4096 38.6 / 30.0 / 23.3 - 23.4, two 13824x5120 105.0 / 78.4 / 55.3
 //     - 51.3, at 32 8192x8192 67.4 / 50.7 / 35.4 - 33.8;
 //     up to 20 million weights, 27 from 8 tokens and 100 from 17 it wins
-//     whatever the activations, so it always runs; with 4 tokens it loses where the columns are few (three 4096x4096
-//     23.1 / 18.2 / 19.6 - 19.2, and 16.5 at u = 0.3), and with 5 to 8 where
-//     the stripes are many and short (16384x1024 at 5 14.0 / 11.3 / 9.3 -
-//     11.8, 28000x700 at 8 14.7 / 12.7 / 11.0 - 17.4);
+//     whatever the activations, so it always runs; with 4 tokens it loses
+//     where the columns are few (three 4096x4096 23.1 / 18.2 / 19.6 - 19.2,
+//     and 16.5 at u = 0.3), and with 5 to 8 where the stripes are many and
+//     short (16384x1024 at 5 14.0 / 11.3 / 9.3 - 11.8, 28000x700 at 8 14.7 /
+//     12.7 / 11.0 - 17.4);
 //   other products win or lose by u: at 8 tokens 5120x13824 34.3 / 25.0 /
 //     20.0 - 26.2, 8192x8192 30.8 / 22.3 / 16.7 - 23.5, 8192x28672 72.8 / 46.7
 //     / 24.4 - 57.2, at 32 28672x8192 153.9 / 104.1 / 62.7 - 82.2. Such calls
@@ -1348,9 +1349,9 @@ int early_first(int batch, int64_t workgroups) {
 // Products that read one input (q, k and v) should take one route, or their
 // call is two launches in a row (with an ungated k and v, 8192x8192 and twice
 // 1024x8192 at 8 tokens and u = 0.7 30.8 - 41.9): so no width beyond 5120
-// counts as small up to 16 tokens, q being large there. A property of the matrix, the batch,
-// the mask and the activations, so a product gives the same bits alone and
-// grouped. SPDP_WIDE overrides the token count from which the form runs (0:
+// counts as small up to 16 tokens, q being large there. A property of the
+// matrix, the batch, the mask and the activations, so a product gives the same
+// bits alone and grouped. SPDP_WIDE overrides the token count from which the form runs (0:
 // never; -n: gated from n tokens, at least 5; for tuning).
 enum Route { kPerColumn, kAllColumns, kGated };
 constexpr int64_t kWideMedium = 100000000;  // weights, the zeros included
@@ -1386,8 +1387,8 @@ float gate_share(const spdp_matrix* h, int batch) {
 // segments (the per-column plan's, so that the partials fit the same
 // workspace), the count that a model of the launch puts at the least time.
 // With m workgroups per CU, three of them resident, a chunk takes
-// 1.6, 1.75 or 2 us (one, two, three resident: from three on the vector ALUs
-// are the limit, 200 instructions per chunk and wave) and a workgroup 3 us
+// 1.6, 1.75 or 2 us (one, two, three resident: the more there are, the more
+// of each other's waits they cover) and a workgroup 3 us
 // and 0.2 us per token (prologue; partials, 8 bytes per row and token).
 // Measured at 8 tokens, 70 % weight sparsity, us by segments: 28672x8192 4 /
 // 5 / 6 / 8: 69 / 75 / 66 / 66; 8192x28672 14 / 16 / 21: 68 / 62 / 66;

@@ -24,14 +24,21 @@
 // are; one chunk ahead they are masked in LDS (inactive entries, and columns
 // past the width, to 0).
 //
-// What bounds it: the vector ALUs. A chunk costs a wave 200 VALU instructions
-// (32 column words: 3 for the address, 1.5 for the select and pack, 0.25 for
-// the operand swap each; the rest requests and masks the next chunk), so
-// three workgroups (six waves per SIMD, hence 80 registers) keep them busy:
-// 28672x8192 at 70 % weight sparsity and 8 / 32 tokens 66 / 85 us against 30
-// us of VALU issue and 42 us for its bytes at the rate of a large copy. The
-// per-column kernels (four words x the tokens' accumulators per wave, two to
-// five waves per SIMD) take 72 / 154.
+// What bounds it: the waves' waiting, and after it vector issue. A chunk costs
+// a wave 200 VALU instructions (32 column words: 3 for the address, 1.5 for
+// the select and pack, 0.25 for the operand swap each; the rest requests and
+// masks the next chunk). Counters over the 13B layer at 8 tokens and the 70B
+// layer at 32 (70 % weight sparsity, gates included): 6.2 and 6.6 VALU
+// instructions per word, 25 and 26 cycles of the 66 and 67 (of 2.4 GHz) that a
+// word takes a SIMD; the waves issue in 23 and 30 % of their cycles and wait in 53 and 50 %
+// (in the loop: for a record's scalar loads and the gather's LDS reads, which
+// share a counter, and at the chunk's barrier). So what helps is waves: three
+// workgroups per CU (six waves per SIMD, hence 80 registers). At 32 tokens
+// the partials add 36 MB written and as many read to 166 MB of input.
+// 28672x8192 at 70 % weight sparsity and 8 / 32 tokens takes 66 / 85 us, 30 us
+// of it VALU issue, 42 its bytes at the rate of a large copy; the per-column
+// kernels (four words x the tokens' accumulators per wave, two to five waves
+// per SIMD) 72 / 154.
 
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
