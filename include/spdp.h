@@ -97,12 +97,13 @@ int spdp_encode_host(const uint16_t* W, int64_t rows, int64_t cols,
  *              (strict). A negative threshold keeps every column; NaN is
  *              SPDP_ERR_INVALID_ARG. NaN activations are never active.
  *              Columns inactive for every token of the batch take no part.
- *              They are not read with up to 4 tokens. With more, a small
- *              matrix (up to 20 million weights; 27 from 8 tokens, 100 from
- *              17) is read whole whatever the threshold, and inactive columns
- *              are multiplied by 0; a larger one is read whole if, in a sample
- *              of X, so many columns are active for some token (30 to 75 % by
- *              size and batch) that this is faster.
+ *              They are not read with up to 4 tokens. With more, a matrix of
+ *              up to 20 million weights (75 from 8 tokens on, 100 from 17) is
+ *              read whole whatever the threshold, and inactive columns are
+ *              multiplied by 0, unless it has many rows for its columns; a
+ *              larger one, or one of many rows from 9 tokens on, is read whole
+ *              if, in a sample of X, so many columns are active for some token
+ *              (30 to 75 % by size and batch) that this is faster.
  *   Y          device, batch x rows fp16, row-major, fully overwritten with
  *              the fp32-accumulated result rounded once to nearest even.
  *              Must not overlap X.
@@ -158,8 +159,8 @@ int spdp_spmspv_noalloc(spdp_handle_t h, const uint16_t* X, int32_t batch,
 
 /*
  * spdp_spmspv_many -- several independent products in one launch (two where
- * spdp_spmspv samples X; products of one width take the same route up to
- * that width's size limits):
+ * spdp_spmspv samples X, or where the products' sizes ask for different
+ * forms; equal shapes take the same):
  * Y[i] = W_i . mask(X[i]) with threshold thresholds[i], for i < count. This
  * is how a decoder issues the projections that read the same layer input
  * (q, k and v; gate and up), whose fixed per-launch latency would otherwise

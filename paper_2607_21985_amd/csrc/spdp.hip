@@ -1320,26 +1320,44 @@ int early_first(int batch, int64_t workgroups) {
 //   per-token masks, 5 tokens: 4096x4096 17.8 / 15.4 / 13.3 - 11.1, three
 //     grouped 31.0 / 26.3 / 26.0 - 19.4, 8192x2048 15.4 / 12.6 / 10.6 - 11.0;
 //     8 tokens: 21.0 / 18.3 / 16.9 - 11.5 and 33.7 / 29.6 / 29.4 - 19.9,
-//     5120x5120 22.0 / 18.0 / 15.8 - 15.1, three 34.6 / 26.9 / 23.7 - 27.2 (a
-//     gate, below, would cost as much as it saves at u = 0.1); 17 tokens:
+//     5120x5120 22.0 / 18.0 / 15.8 - 15.1, three 34.6 / 26.9 / 23.7 - 27.2;
+//     17 tokens:
 //     11008x4096 38.6 / 30.0 / 23.3 - 23.4, two 13824x5120 105.0 / 78.4 / 55.3
 //     - 51.3, at 32 8192x8192 67.4 / 50.7 / 35.4 - 33.8;
 //     up to 20 million weights, 27 from 8 tokens and 100 from 17 it wins
-//     whatever the activations, so it always runs; with 4 tokens it loses
+//     whatever the activations, or loses no more than a gate, so it always
+//     runs; with 4 tokens it loses
 //     where the columns are few (three 4096x4096 23.1 / 18.2 / 19.6 - 19.2,
 //     and 16.5 at u = 0.3), and with 5 to 8 where the stripes are many and
 //     short (16384x1024 at 5 14.0 / 11.3 / 9.3 - 11.8, 28000x700 at 8 14.7 /
 //     12.7 / 11.0 - 17.4);
-//   other products win or lose by u: at 8 tokens 5120x13824 34.3 / 25.0 /
-//     20.0 - 26.2, 8192x8192 30.8 / 22.3 / 16.7 - 23.5, 8192x28672 72.8 / 46.7
-//     / 24.4 - 57.2, at 32 28672x8192 153.9 / 104.1 / 62.7 - 82.2. Such calls
-//     are gated: the all-columns launch looks at a sample of the activations
-//     and leaves the product to a per-column launch behind it where too few
-//     columns are active. That costs 2 us where it runs and 3 to 4 where it
-//     does not (5120x13824 at 8 tokens 28.2 and 23.1 at u = 1 and 0.1), so
-//     products that gain no more stay per-column (28672x8192 at 8 tokens 68.8
-//     - 64.5, two grouped 116.6 - 122.5). With a negative threshold every
-//     column takes part and no gate is needed.
+//   other products win or lose by u. Such calls can be gated: the all-columns
+//     launch looks at a sample of the activations and leaves the product to a
+//     per-column launch behind it where too few columns are active. That costs
+//     2.5 us where it runs, nearly all of it the launch that leaves, and 3 to 5
+//     where it does not, so it has to be worth it. At u = 1 / 0.5 / 0.3 / 0.1,
+//     per-column - all-columns - gated:
+//     from 8 tokens up to 75 million weights with few rows all columns lose
+//     only at u = 0.1, and there little more than a gate costs: 8 tokens
+//     4096x11008 28.2 / 22.6 / - / 18.4 - 20.2 - 22.7 / 26.0 / - / 21.7,
+//     5120x13824 33.6 / 25.3 / 21.9 / 18.3 - 25.7 - 28.1 / 28.7 / 25.4 / 21.7,
+//     8192x8192 30.7 / 22.7 / 19.9 / 16.0 - 22.9 - 25.5 / 26.3 / 23.3 / 19.2; 16
+//     tokens 45.8 / 33.1 / 27.1 / 21.4 - 29.2 - 31.7 / 36.6 / 30.7 / 24.8 and
+//     36.0 / 27.6 / 23.8 / 20.0 - 25.6 - 28.2 / 28.4 / 27.5 / 23.5: not gated;
+//     up to 8 tokens and 60 million weights with many rows a gate gains next
+//     to nothing at u = 1: 5 and 8 tokens two 11008x4096 33.1 / 24.6 / - / 17.7
+//     - 30.0 - 33.3 / 29.3 / - / 22.1 and 34.9 / 27.5 / - / 20.7 - 31.2 - 34.3 /
+//     32.0 / - / 25.0, two 14336x4096 40.3 / 29.5 / - / 20.4 - 36.6 - 40.2 / 34.1
+//     / - / 24.9 and 44.1 / 33.1 / - / 24.6 - 37.5 - 41.2 / 37.6 / - / 28.8:
+//     per column. Nor does it with more than 100 million (28672x8192 at 8
+//     tokens 68.8 - 64.5, two grouped 116.6 - 122.5), but where the columns are
+//     more (8192x28672 72.8 / 46.7 / - / 24.4 - 57.2);
+//     the rest is gated: two 13824x5120 at 8 tokens 53.0 / 36.7 / 30.5 / 23.8 -
+//     41.4 - 44.8 / 41.1 / 34.8 / 28.1, two 14336x4096 at 16 61.2 / 46.2 / - /
+//     32.6 - 43.3 - 46.1 / 51.1 / - / 37.4, 28672x8192 at 32 153.9 / 104.1 / - /
+//     62.7 - 82.2; with 5 to 7 tokens also few rows, whose groups lose more
+//     (two 3584x8192 at 5 27.9 / 21.9 / - / 17.0 - 25.4 - 28.4 / 26.1 / - / 21.1).
+//     With a negative threshold every column takes part and no gate is needed.
 //   one mask for the batch: 8 and 16 tokens 4096x4096 21.2 / 18.3 / 16.7 -
 //     12.6 and 25.9 / 23.1 / 21.6 - 15.7, three grouped 34.3 / 29.2 / 29.2 -
 //     20.6 and 39.2 / 35.8 / 33.6 - 24.5; larger products lose at the shares
@@ -1348,13 +1366,17 @@ int early_first(int batch, int64_t workgroups) {
 //     tokens 20.7 - 22.9).
 // Products that read one input (q, k and v) should take one route, or their
 // call is two launches in a row (with an ungated k and v, 8192x8192 and twice
-// 1024x8192 at 8 tokens and u = 0.7 30.8 - 41.9): so no width beyond 5120
-// counts as small up to 16 tokens, q being large there. A property of the
-// matrix, the batch, the mask and the activations, so a product gives the same
-// bits alone and grouped. SPDP_WIDE overrides the token count from which the form runs (0:
-// never; -n: gated from n tokens, at least 5; for tuning).
+// 1024x8192 at 8 tokens and u = 0.7 30.8 - 41.9): so with few rows for their
+// columns they count as the q that may stand beside them from 8 tokens on
+// (the three at 8 and 16 tokens at u = 1 / 0.5 / 0.1 35.3 / 27.7 / 21.3 - 30.4
+// and 47.4 / 37.6 / 30.0 - 34.6), and below 8 no width beyond 5120 counts as
+// small. A property of the matrix, the batch, the mask and the activations, so
+// a product gives the same bits alone and grouped. SPDP_WIDE overrides the
+// token count from which the form runs (0: never; -n: gated from n tokens, at
+// least 5; for tuning).
 enum Route { kPerColumn, kAllColumns, kGated };
-constexpr int64_t kWideMedium = 100000000;  // weights, the zeros included
+// weights, the zeros included
+constexpr int64_t kWideTall = 60000000, kWideLarge = 75000000, kWideMost = 100000000;
 constexpr int64_t kWideSmallCols = 5120;
 Route choose_route(const spdp_matrix* h, int batch, bool bmask, int32_t code) {
   if (!h->d_rec || !h->finite || batch < 2 || use_mfma(batch)) return kPerColumn;
@@ -1368,18 +1390,23 @@ Route choose_route(const spdp_matrix* h, int batch, bool bmask, int32_t code) {
   if (bmask) return small && batch >= 8 && batch <= 16 ? kAllColumns : kPerColumn;
   if (batch < 5) return kPerColumn;
   if (small) return batch <= 8 && h->rows > 8 * h->cols ? kPerColumn : kAllColumns;
-  if (batch > 16 && weights <= kWideMedium) return kAllColumns;
-  if (weights > kWideMedium && batch <= 8 && (batch < 8 || h->rows > h->cols)) return kPerColumn;
+  if (batch > 16 && weights <= kWideMost) return kAllColumns;
+  const bool tall = 2 * h->rows > 5 * h->cols;
+  if (tall && batch <= 8 && weights <= kWideTall) return code < 0 ? kAllColumns : kPerColumn;
+  const int64_t with_q = 4 * h->rows <= h->cols ? h->cols * h->cols : weights;
+  if (!tall && batch >= 8 && with_q <= kWideLarge) return kAllColumns;
+  if (weights > kWideMost && batch <= 8 && (batch < 8 || h->rows > h->cols)) return kPerColumn;
   return code < 0 ? kAllColumns : kGated;
 }
 
 // The share of the sample's columns from which a gated product runs in the
-// all-columns form: about where the two tie (at 8 tokens u = 0.56 to 0.7; at
-// 16 0.5 to 0.6, but 0.8 with many rows, 11008x4096 and 28672x8192 grouped;
-// at 32 up to 0.34).
+// all-columns form: about where the two tie, the gate's price on either side
+// included. From the figures above up to 8 tokens u = 0.35 to 0.7 (more for
+// groups), up to 16 0.4 to 0.6 (13824x5120 at 12 tokens, two grouped 0.4, one
+// 0.5), but 0.8 for two 28672x8192; at 32 up to 0.34.
 float gate_share(const spdp_matrix* h, int batch) {
-  if (batch <= 8) return 0.7f;
-  if (batch <= 16) return h->rows > 2 * h->cols ? 0.75f : 0.5f;
+  if (batch <= 8) return 0.6f;
+  if (batch <= 16) return h->rows > 2 * h->cols && h->rows * h->cols > kWideMost ? 0.75f : 0.5f;
   return 0.3f;
 }
 

@@ -217,11 +217,52 @@ def test_encode_without_host_memory_for_the_records(fake_hip):
     assert out == {"0": True, "388": False, "live": 0}, out
 
 
+# what one product takes: "columns" (the per-column kernels), "wide" (the
+# all-columns form) or both (gated)
+ROUTES = [
+    # rows, cols, tokens, route
+    (2048, 2048, 4, ["columns"]), (2048, 2048, 5, ["wide"]), (2048, 2048, 8, ["wide"]), (2048, 2048, 32, ["wide"]),
+    (20000, 1000, 8, ["columns"]), (20000, 1000, 9, ["wide"]),              # many short stripes
+    (5120, 5120, 7, ["wide", "columns"]), (5120, 5120, 8, ["wide"]),
+    (1024, 8192, 5, ["wide", "columns"]), (1024, 8192, 8, ["wide"]),         # k, beside a q of 8192 rows
+    (600, 8700, 8, ["wide", "columns"]), (600, 8700, 17, ["wide"]),          # beside one of 8700
+    (4096, 11008, 7, ["wide", "columns"]), (4096, 11008, 8, ["wide"]), (4096, 11008, 16, ["wide"]),
+    (11008, 4096, 5, ["columns"]), (11008, 4096, 8, ["columns"]), (11008, 4096, 9, ["wide", "columns"]),
+    (11008, 4096, 17, ["wide"]),
+    (13824, 5120, 5, ["wide", "columns"]), (13824, 5120, 8, ["wide", "columns"]), (13824, 5120, 17, ["wide"]),
+    (5120, 13824, 7, ["wide", "columns"]), (5120, 13824, 8, ["wide"]),
+    (28672, 4000, 7, ["columns"]), (28672, 4000, 8, ["columns"]), (28672, 4000, 9, ["wide", "columns"]),
+    (28672, 4000, 32, ["wide", "columns"]),
+    (4000, 28672, 7, ["columns"]), (4000, 28672, 8, ["wide", "columns"]),
+]
+
+
+def test_routes(fake_hip):
+    # the rule's lines, from both sides; with a negative threshold every
+    # column takes part, and nothing is gated
+    out = run(fake_hip, f"""
+    mats = {{}}
+    for rows, cols, tokens, _ in {ROUTES!r}:
+        if (rows, cols) not in mats:
+            mats = {{(rows, cols): ones(rows, cols, (256, 16), 0.002)}}
+        m = mats[rows, cols]
+        for t in (0.5, -1.0):
+            log()
+            assert many([m], tokens, 0, [t]) == 0
+            out[f"{{rows}} {{cols}} {{tokens}} {{t}}"] = ["wide" if "wide" in n else "columns" for n, g in launches()]
+    """)
+    for rows, cols, tokens, want in ROUTES:
+        assert out[f"{rows} {cols} {tokens} 0.5"] == want, (rows, cols, tokens, out[f"{rows} {cols} {tokens} 0.5"])
+        assert len(out[f"{rows} {cols} {tokens} -1.0"]) == 1
+        if len(want) == 2:
+            assert out[f"{rows} {cols} {tokens} -1.0"] == ["wide"]
+
+
 def test_launches_of_a_grouped_call(fake_hip):
-    # q, k and v of the 70B layer: one launch where no product is gated (4
-    # tokens, one mask for the batch), and never more than two, the second
-    # only with products that the first is a gate for; every column kept
-    # (a negative threshold): one
+    # q, k and v of the 70B layer: one launch where no product is gated (up
+    # to 4 tokens, from 8 on, one mask for the batch), and never more than
+    # two, the second only with products that the first is a gate for; every
+    # column kept (a negative threshold): one
     out = run(fake_hip, """
     q = ones(8192, 8192, (256, 16), 0.02)
     k = ones(1024, 8192, (256, 16), 0.02, 1)
@@ -232,30 +273,22 @@ def test_launches_of_a_grouped_call(fake_hip):
                 log()
                 assert many([q, k, v], tokens, mask, [t] * 3) == 0
                 out[f"{tokens} {mask} {t}"] = [("wide" if "wide" in n else "columns", g[1]) for n, g in launches()]
-    s = ones(2048, 2048, (256, 16), 0.02)
-    for tokens in (4, 5, 8, 32):
-        log()
-        assert many([s], tokens) == 0
-        out[f"small {tokens}"] = [("wide" if "wide" in n else "columns", g[1]) for n, g in launches()]
     """)
     for key, got in out.items():
-        if key.startswith("small"):
-            want = [["columns" if key == "small 4" else "wide", 1]]
+        tokens, mask, t = key.split()
+        if int(tokens) < 5 or mask == "1":
+            want = [["columns", 3]]
+        elif t == "-1.0" or int(tokens) >= 8:
+            want = [["wide", 3]]
         else:
-            tokens, mask, t = key.split()
-            if int(tokens) < 5 or mask == "1":
-                want = [["columns", 3]]
-            elif t == "-1.0" or int(tokens) > 16:
-                want = [["wide", 3]]
-            else:
-                want = [["wide", 3], ["columns", 3]]
+            want = [["wide", 3], ["columns", 3]]
         assert got == want, (key, got)
 
 
 def test_a_call_that_cannot_be_launched_launches_nothing(fake_hip):
     # a gated product is two launches: what can fail is asked before the first
     out = run(fake_hip, """
-    m = ones(300, 6400, (256, 16), 1.0)  # dense: more than 64 KB of LDS
+    m = ones(300, 8800, (256, 16), 1.0)  # dense: more than 64 KB of LDS
     hip.fake_fail_attribute(1)
     log()
     out["status"] = many([m], 8)
