@@ -1,6 +1,6 @@
 // Decode in which every column takes part (the all-columns form): for batches
-// whose tokens' active columns, taken together, are nearly all columns, and
-// for products so small that finding them costs more than they do
+// whose tokens' active columns, taken together, are most columns, and for
+// products where leaving columns out gains less than finding out which
 // (choose_route in spdp.hip). A column that no token has active is then
 // multiplied by zeros instead of being skipped, and the values stream as
 // contiguous runs, with no list of columns, into the expansion of expand.h
@@ -13,10 +13,9 @@
 // The grid is the per-column kernels' in shape (workgroup x is stripe
 // x / segments, segment x mod segments, of product blockIdx.y; the segments
 // are this form's own, wide_seg_chunks), and so is the split-K exchange. Eight
-// waves: wave w expands bitmap word w mod 4 (64
-// rows) of the groups 2 (w / 4), 2 (w / 4) + 1 of every chunk (64 columns)
-// and multiplies them with all tokens; the two halves of the chunk are added
-// once, at the end.
+// waves: wave w expands bitmap word w mod 4 (64 rows) of the groups 2 (w / 4),
+// 2 (w / 4) + 1 of every chunk (64 columns) and multiplies them with all
+// tokens; the two halves of the chunk are added once, at the end.
 //
 // A chunk's values arrive by global->LDS DMA one chunk ahead (two slots; three
 // slots leave room for two workgroups per CU instead of three at 50 % weight
@@ -29,10 +28,10 @@
 // the select and pack, 0.25 for the operand swap each; the rest requests and
 // masks the next chunk). Counters over the 13B layer at 8 tokens and the 70B
 // layer at 32 (70 % weight sparsity, gates included): 6.2 and 6.6 VALU
-// instructions per word, 25 and 26 cycles of the 66 and 67 (of 2.4 GHz) that a
-// word takes a SIMD; the waves issue in 23 and 30 % of their cycles and wait in 53 and 50 %
-// (in the loop: for a record's scalar loads and the gather's LDS reads, which
-// share a counter, and at the chunk's barrier). So what helps is waves: three
+// instructions per word, 25 and 26 cycles of the 63 and 65 (of 2.4 GHz) that a
+// word takes a SIMD; the waves issue in 23 and 30 % of their cycles and wait in
+// 53 and 50 % (in the loop: for a record's scalar loads and the gather's LDS
+// reads, which share a counter, and at the chunk's barrier). So what helps is waves: three
 // workgroups per CU (six waves per SIMD, hence 80 registers). At 32 tokens
 // the partials add 36 MB written and as many read to 166 MB of input.
 // 28672x8192 at 70 % weight sparsity and 8 / 32 tokens takes 66 / 85 us, 30 us
