@@ -1008,7 +1008,7 @@ def main():
 
 # ---------------------------------------------------------------------------
 # rocprofv3 summaries (profiles/*.txt) from the raw outputs of the commands
-# below, written under DIR on the GPU machine:
+# below, written under DIR on a machine with the GPU:
 #   rocprofv3 --kernel-trace --stats --output-format csv -d DIR/trace_TAG -o run -- \
 #       python3 bench.py --profile-only ARGS > DIR/trace_TAG.log
 #   rocprofv3 --pmc PASS_R --output-format csv -d DIR/pmcR_TAG -o run -- \
@@ -1067,7 +1067,7 @@ def summarize_prefill(d, prof_dir):
     with open(os.path.join(d, "trace_prefill.log")) as fh:
         pj = next(json.loads(l) for l in fh if l.startswith("{") and "prefill_only" in l)
     rows = list(csv.DictReader(open(os.path.join(d, "trace_prefill", "run_kernel_stats.csv"))))
-    out = ["# spdp_spmm (prefill) kernels", "", "command (GPU box, repository root, TMPDIR=/tmp):",
+    out = ["# spdp_spmm (prefill) kernels", "", "command (on the MI355X, repository root, TMPDIR=/tmp):",
            f"  rocprofv3 --kernel-trace --stats --output-format csv -d {d}/trace_prefill -o run -- "
            f"python3 bench.py --prefill-only > {d}/trace_prefill.log", "",
            "kernel_stats (durations in ns):", "Name | Calls | AverageNs | MinNs | MaxNs"]
@@ -1105,7 +1105,7 @@ def summarize_sq(d, tag, pj, prof_dir, sha, per_launch):
     words = pj["line_model_per_launch"]["bitmap"][0] / 8.0
     wc = mean("SQ_WAVE_CYCLES")
     out = [f"# shader-sequencer counters of spmspv_kernel: {tag}", "",
-           "commands (GPU box, repository root, TMPDIR=/tmp), one counter pass per run:"] + cmds + [
+           "commands (on the MI355X, repository root, TMPDIR=/tmp), one counter pass per run:"] + cmds + [
            "", f"mean per spMspV launch ({len(cs['SQ_WAVES'][0])} kernel dispatches in the first pass, "
                f"{per_launch:g} per launch):"]
     for p in PASS_S:
@@ -1139,7 +1139,7 @@ def summarize_profiles(d, prof_dir=None):
     for tag in tags:
         pj = _profile_line(os.path.join(d, f"trace_{tag}.log"))
         rows = list(csv.DictReader(open(os.path.join(d, f"trace_{tag}", "run_kernel_stats.csv"))))
-        out = [f"# spmspv_kernel: {tag}", "", "command (GPU box, repository root, TMPDIR=/tmp):",
+        out = [f"# spmspv_kernel: {tag}", "", "command (on the MI355X, repository root, TMPDIR=/tmp):",
                "  " + _cmd("trace", d, tag, pj), "",
                "kernel_stats (durations in ns):", "Name | Calls | AverageNs | MinNs | MaxNs"]
         for r in rows:
@@ -1194,7 +1194,7 @@ def summarize_profiles(d, prof_dir=None):
         alg_rd = sum(a for k, (a, l) in lm.items() if k != "y")
         partial_w = max(wr - y, 0.0)
         out = [f"# HBM traffic of spmspv_kernel: {tag}", "",
-               "commands (GPU box, repository root, TMPDIR=/tmp), one counter pass per run:",
+               "commands (on the MI355X, repository root, TMPDIR=/tmp), one counter pass per run:",
                "  " + _cmd("pmcR", d, tag, pjr), "  " + _cmd("pmcW", d, tag, _profile_line(os.path.join(d, f"pmcW_{tag}.log"))),
                "",
                f"reference: the streaming-read kernel over {ref} bytes (16-byte loads):",
