@@ -1321,16 +1321,14 @@ int early_first(int batch, int64_t workgroups) {
 //     grouped 31.0 / 26.3 / 26.0 - 19.4, 8192x2048 15.4 / 12.6 / 10.6 - 11.0;
 //     8 tokens: 21.0 / 18.3 / 16.9 - 11.5 and 33.7 / 29.6 / 29.4 - 19.9,
 //     5120x5120 22.0 / 18.0 / 15.8 - 15.1, three 34.6 / 26.9 / 23.7 - 27.2;
-//     17 tokens:
-//     11008x4096 38.6 / 30.0 / 23.3 - 23.4, two 13824x5120 105.0 / 78.4 / 55.3
-//     - 51.3, at 32 8192x8192 67.4 / 50.7 / 35.4 - 33.8;
+//     17 tokens 11008x4096 38.6 / 30.0 / 23.3 - 23.4, two 13824x5120 105.0 /
+//     78.4 / 55.3 - 51.3, at 32 8192x8192 67.4 / 50.7 / 35.4 - 33.8;
 //     up to 20 million weights, 27 from 8 tokens and 100 from 17 it wins
 //     whatever the activations, or loses no more than a gate, so it always
-//     runs; with 4 tokens it loses
-//     where the columns are few (three 4096x4096 23.1 / 18.2 / 19.6 - 19.2,
-//     and 16.5 at u = 0.3), and with 5 to 8 where the stripes are many and
-//     short (16384x1024 at 5 14.0 / 11.3 / 9.3 - 11.8, 28000x700 at 8 14.7 /
-//     12.7 / 11.0 - 17.4);
+//     runs; with 4 tokens it loses where the columns are few (three 4096x4096
+//     23.1 / 18.2 / 19.6 - 19.2, and 16.5 at u = 0.3), and with 5 to 8 where
+//     the stripes are many and short (16384x1024 at 5 14.0 / 11.3 / 9.3 - 11.8,
+//     28000x700 at 8 14.7 / 12.7 / 11.0 - 17.4);
 //   other products win or lose by u. Such calls can be gated: the all-columns
 //     launch looks at a sample of the activations and leaves the product to a
 //     per-column launch behind it where too few columns are active. That costs
